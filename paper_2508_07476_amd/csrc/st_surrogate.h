@@ -144,7 +144,15 @@ hipError_t launch_sg_conv_bwd(const SgConvParams& p, hipStream_t stream);
 // Stored activations and gradients are [N][32] bf16, channel-last.  Row r of a
 // volume of nz x ny x nx voxels (nx <= 32) holds voxels r * nx .. r * nx + nx - 1.
 constexpr int kSgTrainMaxX = 32;          // rows of at most 32 voxels (one MFMA K step)
-constexpr int kSgWgradBlocks = 256;       // blocks of the weight-gradient kernels
+constexpr int kSgWgradBlocks = 256;       // most blocks of the weight-gradient kernels (one per CU)
+constexpr int kSgWgradRows = 8;           // rows (y) of one plane a block takes
+// z planes per block of the weight-gradient kernels: as few as keep the launch
+// within kSgWgradBlocks blocks.
+inline int64_t sg_wgrad_planes(int64_t nz, int64_t ny) {
+  const int64_t y_tiles = (ny + kSgWgradRows - 1) / kSgWgradRows;  // ny <= 32: at most 4
+  const int64_t chunks = kSgWgradBlocks / y_tiles;
+  return (nz + chunks - 1) / chunks;
+}
 constexpr int kSgHeadSums = 5 * kSgChannels + 5 + 6;  // head gradient (Wh, bh) and six loss sums
 constexpr int kSgTrainStats = 8;          // dir, fa, conf, total loss, sum w, within, mean angle (deg), count
 
@@ -172,7 +180,7 @@ struct SgWgradParams {
   const float* scale_offset;
   float* partial;         // [blocks][27 * 32 * 32 + 32] (layers 2..5) or [blocks][32 * 27 + 32] (layer 1)
   int64_t nz, ny, nx;     // the stacked volume (nx <= kSgTrainMaxX)
-  int64_t rows_per_block;
+  int64_t rows_per_block; // kSgWgradRows rows (y) of each of its planes (z): y tile fastest, then z chunk
 };
 hipError_t launch_sg_wgrad(const SgWgradParams& p, int blocks, hipStream_t stream);
 hipError_t launch_sg_wgrad1(int dtype, const SgWgradParams& p, int blocks, hipStream_t stream);

@@ -614,8 +614,8 @@ extern "C" int st_surrogate_grad(const void* patches, int dtype, int64_t npatch,
   const int C = st::kSgChannels;
   const int64_t P = patch;
   const int64_t nz = npatch * P, ny = P, nx = P;
-  const int64_t rows = nz * ny;
-  const int wb = static_cast<int>(std::min<int64_t>(st::kSgWgradBlocks, rows));
+  const int64_t wplanes = st::sg_wgrad_planes(nz, ny);
+  const int wb = static_cast<int>((ny + st::kSgWgradRows - 1) / st::kSgWgradRows * ((nz + wplanes - 1) / wplanes));
   const float* blob = params;
   const char* stage = "surrogate_pack";
   hipError_t e = hipSuccess;
@@ -664,7 +664,7 @@ extern "C" int st_surrogate_grad(const void* patches, int dtype, int64_t npatch,
     std::memset(&wg, 0, sizeof(wg));
     wg.partial = wpart;
     wg.nz = nz; wg.ny = ny; wg.nx = nx;
-    wg.rows_per_block = (rows + wb - 1) / wb;
+    wg.rows_per_block = st::kSgWgradRows * wplanes;
     int cur = 0;
     for (int layer = st::kSgLayers; layer >= 2 && e == hipSuccess; --layer) {
       wg.g = gbuf[cur];
