@@ -10,8 +10,14 @@
 // four waves per SIMD without spilling, else 4; a 4-row variant is also built
 // up to radius 6 for the batch autotuner).  For every input plane (z halo of R on
 // each side, reflected at the faces) the (TY + 2R) x (64 + 2R) input tile is
-// staged in LDS, in two buffers used by alternate planes; the next plane's
-// loads are issued before the current plane is filtered.  Each wave filters
+// staged in LDS, in two buffers used by alternate planes.  A plane's loads stay
+// raw in registers (converted only when staged: a conversion beside the load
+// waits for it) and have a whole plane's work to arrive: they are issued between
+// the x and the z filter of the plane two before and staged at the same point of
+// the next.  What bounds the pass is VALU issue (62 % of the cycles) and
+// LDS reads at a clock held down by power; with the loads waited for where they
+// were issued it took 1389 us at radius 6 on 512^3 u16, against 1245 (7258 against
+// 6138 at radius 8 on 512 x 1024 x 1024).  Each wave filters
 // along y the 64 + 2R columns of its own tile row, which only it reads in the
 // x filter, so one block barrier per plane (after the staging) suffices: a
 // wave that writes plane j + 1's buffer has passed plane j's barrier, and one
@@ -73,24 +79,30 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
     const int gx = reflect_lane(static_cast<int>(x0) - R + col, static_cast<int>(nx));
     off[j] = gy * static_cast<int>(nx) + gx;
   }
-  float pf[NSTAGE];
+  // the input plane in flight, as loaded: a conversion here would wait for it
+  Tin pf[NSTAGE];
   auto fetch = [&](int zi) {  // loads of input plane zi into pf
     const Tin* src = vol + static_cast<int64_t>(reflect_lane(zi, nzi)) * plane;
 #pragma unroll
-    for (int j = 0; j < NSTAGE; ++j) pf[j] = static_cast<float>(src[off[j]]);  // halo re-read by neighbours: keep cached
+    for (int j = 0; j < NSTAGE; ++j) pf[j] = src[off[j]];  // halo re-read by neighbours: keep cached
   };
 
-  // Stage plane step j (already fetched into pf) and filter it along y then x;
-  // returns the three partial results of this thread's column, and prefetches
-  // plane `next`.
-  auto filter_plane = [&](int j, int next, bool has_next, double& a, double& bq, double& c) {
+  auto stage = [&](int j) {  // the fetched plane into step j's buffer
     float* rb = raw[j & 1];
 #pragma unroll
     for (int t = 0; t < NSTAGE; ++t) {
       const int s = tid + NT * t;
-      if (s < RX * RY) rb[s] = pf[t];
+      if (s < RX * RY) rb[s] = static_cast<float>(pf[t]);
     }
-    if (has_next) fetch(next);
+  };
+
+  // Filter plane step j (staged) along y then x: the three partial results of
+  // this thread's column.  Then stage plane step j + 1, whose loads have been in
+  // flight since the step before, and issue those of step j + 2: the wait for
+  // loads also waits for the products stored before them, which by then had the
+  // two filters' time to leave.
+  auto filter_plane = [&](int j, int nplanes, double& a, double& bq, double& c) {
+    const float* rb = raw[j & 1];
     __syncthreads();
     // y filter of the wave's own row (columns tx and tx + 64 of RX): only this
     // wave reads it, so no block barrier separates it from the x filter
@@ -124,6 +136,10 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
     // materialise the three results here: otherwise the compiler sinks these
     // sums towards their use in the z filter and keeps every LDS value alive
     asm volatile("" : "+v"(ga), "+v"(gb), "+v"(dc));
+    if (j + 1 < nplanes) {
+      stage(j + 1);
+      if (j + 2 < nplanes) fetch(z0 - R + j + 2);
+    }
     a = ga;   // Gx Gy V   -> Dz gives g_z
     bq = gb;  // Gx Dy V   -> Gz gives g_y
     c = dc;   // Dx Gy V   -> Gz gives g_x
@@ -137,15 +153,17 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
   // input plane j - 2R + k at plane step j; the plane loop is expanded W times
   // so that every slot index is static (no register moves)
   double wa[W], wb[W], wc[W];
+  const int nplanes = len + 2 * R;  // at least 3
   fetch(z0 - R);
-  const int nplanes = len + 2 * R;
+  stage(0);
+  fetch(z0 - R + 1);
 #pragma unroll 1
   for (int jb = 0; jb < nplanes; jb += W) {  // block-uniform trip count
     auto step = [&]<int J>(std::integral_constant<int, J>) {
       const int j = jb + J;
       if (j < nplanes) {
         double a, bq, c;
-        filter_plane(j, z0 - R + j + 1, j + 1 < nplanes, a, bq, c);
+        filter_plane(j, nplanes, a, bq, c);
         constexpr int S = (J + 2 * R) % W;
         wa[S] = a;
         wb[S] = bq;
