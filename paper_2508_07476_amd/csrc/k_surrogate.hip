@@ -12,15 +12,17 @@
 // ends with 4 consecutive output channels of one voxel, an 8-byte channel-last
 // store.
 //
-// Two kernels.  The first layer and the training passes stream their weights:
-// a block of 8 waves owns 8 (y) x 32 (x) output voxels and marches through a
-// chunk of z planes; the layer's weights are staged in LDS once per block (27 x
-// 32 x 32 bf16, tap-major, output channel, input channel) and the input planes
-// live in a ring of 3 LDS planes of 10 x 34 voxels (faces clamped), the next
-// plane's loads issued before the current plane's matrix products.  The
-// inference layers 2..5 keep their weights in registers (k_sg_conv_ws, below).
+// Two kernels.  The first layer (k_sg_conv): a block of 8 waves owns 8 (y) x 32
+// (x) output voxels and marches through a chunk of z planes; its weights (32 x 32
+// bf16) and a ring of 3 input planes of 10 x 34 voxels (faces clamped) live in
+// LDS.  The 32 -> 32 layers (k_sg_conv_ws, below: inference and training) keep
+// their weights in registers.  Both issue the next plane's loads before the
+// current plane's matrix products, and both take z chunks by sg_zchunk.
 // The last layer's epilogue evaluates the head, the normalisation, FA,
 // confidence, the mask and the helix / intrusion angles.
+#include <algorithm>
+#include <utility>
+
 #include "st_device.h"
 #include "st_surrogate.h"
 
@@ -59,10 +61,9 @@ __global__ void k_sg_pack(const float* blob, __bf16* w1, __bf16* w25) {
 // Outputs of one voxel from its five head values o = bh + Wh x5: unit fibre
 // vector with the canonical sign, FA and confidence (sigmoids), the helix and
 // intrusion angles; zeros outside the mask.
-__device__ __forceinline__ void head_outputs(const SgConvParams& p, const float o[5], int64_t z, int64_t yo,
-                                             int64_t xv) {
+__device__ __forceinline__ void head_outputs(const SgConvParams& p, const float o[5], bool inside, int64_t z,
+                                             int64_t yo, int64_t xv) {
   const int64_t vox = (z * p.ny + yo) * p.nx + xv;
-  const bool inside = p.mask == nullptr || p.mask[vox] != 0;
   float ez = 0.f, ey = 0.f, ex = 0.f, fa = 0.f, conf = 0.f, ha = 0.f, ia = 0.f;
   if (inside) {
     const float nn = o[0] * o[0] + o[1] * o[1] + o[2] * o[2];
@@ -89,17 +90,28 @@ __device__ __forceinline__ void head_outputs(const SgConvParams& p, const float 
   if (p.ia) p.ia[vox] = ia;
 }
 
-// Streaming-weights layer: the first layer (FIRST: input is the raw volume, one
-// channel), and the training passes (hidden layers storing their activations;
-// BWD, the backward data pass: no bias, and the output is multiplied by the
-// ReLU mask of p.prev (the forward activation at the output voxel) instead of
-// passing through ReLU).
-template <bool FIRST, typename Tin, bool BWD = false>
+// z planes per block for `tiles` x-y tiles and `planes` output planes.  A block
+// pays about `head` planes' time before its first output (the ring's first planes,
+// the weights), and per_cu blocks run on a CU, so the launch takes about
+// ceil(blocks / (256 per_cu)) rounds of (chunk + head): the chunk that makes this
+// least, the largest such up to `most`.  A fixed 16 left a 48^3 volume's layers
+// with 18 blocks: 83 us a layer, against 18.
+int64_t sg_zchunk(int64_t tiles, int64_t planes, int64_t per_cu, int64_t most) {
+  constexpr int64_t kHead = 3;
+  int64_t best = 1, cost = INT64_MAX;
+  for (int64_t c = 1; c <= std::min(planes, most); ++c) {
+    const int64_t blocks = tiles * ((planes + c - 1) / c);
+    const int64_t t = (blocks + 256 * per_cu - 1) / (256 * per_cu) * (c + kHead);
+    if (t <= cost) { cost = t; best = c; }
+  }
+  return best;
+}
+
+// First layer: the input is the raw volume, one channel.
+template <typename Tin>
 __global__ __launch_bounds__(NT) void k_sg_conv(const SgConvParams p) {
-  constexpr int WN = FIRST ? C * 32 : 27 * C * C;             // bf16 weights staged
-  constexpr int AN = FIRST ? 3 * PLANE_VOX : 3 * PLANE_VOX * C;  // bf16 activations staged
-  __shared__ __attribute__((aligned(16))) __bf16 wl[WN];
-  __shared__ __attribute__((aligned(16))) __bf16 al[AN];
+  __shared__ __attribute__((aligned(16))) __bf16 wl[C * 32];
+  __shared__ __bf16 al[3 * PLANE_VOX];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t b = blockIdx.x;
@@ -114,71 +126,48 @@ __global__ __launch_bounds__(NT) void k_sg_conv(const SgConvParams p) {
 
   // weights: 16-byte chunks
   {
-    const bf16x8* src = reinterpret_cast<const bf16x8*>(FIRST ? p.w1 : p.w);
+    const bf16x8* src = reinterpret_cast<const bf16x8*>(p.w1);
     bf16x8* dst = reinterpret_cast<bf16x8*>(wl);
-    for (int i = tid; i < WN / 8; i += NT) dst[i] = src[i];
+    for (int i = tid; i < C * 32 / 8; i += NT) dst[i] = src[i];
   }
 
-  const double in_scale = FIRST ? static_cast<double>(p.scale_offset[0]) : 0.0;
-  const double in_offset = FIRST ? static_cast<double>(p.scale_offset[1]) : 0.0;
+  const double in_scale = static_cast<double>(p.scale_offset[0]);
+  const double in_offset = static_cast<double>(p.scale_offset[1]);
 
-  // staging of one input plane (index zi, clamped) into ring slot s
-  // FIRST: one value per voxel (normalised, bf16); else 4 chunks of 16 bytes per voxel
-  constexpr int PER = FIRST ? (PLANE_VOX + NT - 1) / NT : (PLANE_VOX * 4 + NT - 1) / NT;
-  // the raw volume is whole; `in` starts at plane in_z0
-  auto plane_base = [&](int64_t zi) { return (clampi(zi, nz) - (FIRST ? 0 : p.in_z0)) * ny * nx; };
-  auto load_plane = [&](int64_t zi, bf16x8 (&pf)[PER], float (&pv)[PER]) {
-    const int64_t pb = plane_base(zi);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int c = tid + NT * j;
-      if constexpr (FIRST) {
-        const int vi = c < PLANE_VOX ? c : PLANE_VOX - 1;
-        const int row = vi / RX, col = vi % RX;
-        const int64_t g = pb + clampi(y0 - 1 + row, ny) * nx + clampi(x0 - 1 + col, nx);
-        pv[j] = static_cast<float>(static_cast<const Tin*>(p.vol)[g]);
-      } else {
-        const int cc = c < PLANE_VOX * 4 ? c : PLANE_VOX * 4 - 1;
-        const int vi = cc >> 2, part = cc & 3;
-        const int row = vi / RX, col = vi % RX;
-        const int64_t g = pb + clampi(y0 - 1 + row, ny) * nx + clampi(x0 - 1 + col, nx);
-        pf[j] = reinterpret_cast<const bf16x8*>(p.in + g * C)[part];
-      }
-    }
+  // staging of one input plane (index zi, clamped): one value per voxel
+  constexpr int PER = (PLANE_VOX + NT - 1) / NT;
+  static_assert(PER == 1, "one staged value per thread");
+  const int vi = tid < PLANE_VOX ? tid : PLANE_VOX - 1;
+  const int64_t off = clampi(y0 - 1 + vi / RX, ny) * nx + clampi(x0 - 1 + vi % RX, nx);
+  auto load_plane = [&](int64_t zi) {
+    return static_cast<float>(static_cast<const Tin*>(p.vol)[clampi(zi, nz) * ny * nx + off]);
   };
-  auto store_plane = [&](int s, const bf16x8 (&pf)[PER], const float (&pv)[PER]) {
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int c = tid + NT * j;
-      if constexpr (FIRST) {
-        if (c < PLANE_VOX)  // float64 affine map (exact product, one rounding), then float32, then bf16
-          al[s * PLANE_VOX + c] = static_cast<__bf16>(
-              static_cast<float>(fma(static_cast<double>(pv[j]), in_scale, in_offset)));
-      } else {
-        if (c < PLANE_VOX * 4) reinterpret_cast<bf16x8*>(al)[s * PLANE_VOX * 4 + c] = pf[j];
-      }
-    }
+  auto store_plane = [&](int s, float v) {
+    if (tid < PLANE_VOX)  // float64 affine map (exact product, one rounding), then float32, then bf16
+      al[s * PLANE_VOX + tid] =
+          static_cast<__bf16>(static_cast<float>(fma(static_cast<double>(v), in_scale, in_offset)));
   };
 
-  bf16x8 pf[PER];
-  float pv[PER];
-  load_plane(z0 - 1, pf, pv);
-  store_plane(0, pf, pv);
-  load_plane(z0, pf, pv);
-  store_plane(1, pf, pv);
-  load_plane(z0 + 1, pf, pv);
-  store_plane(2, pf, pv);
+  store_plane(0, load_plane(z0 - 1));
+  store_plane(1, load_plane(z0));
+  store_plane(2, load_plane(z0 + 1));
   __syncthreads();
 
   const int li = lane & 15, lk = lane >> 4;
   const int64_t yo = y0 + wave;
-  const float* bias = p.bias;
+  float bias[2][4];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bias[m][r] = p.bias[16 * m + 4 * lk + r];
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), as in k_sg_conv_ws
 #pragma unroll 1
   for (int64_t z = z0; z < z1; ++z) {
     // ring slot of input plane z + d is (z - z0 + 1 + d) mod 3
     const int s0 = static_cast<int>((z - z0) % 3);  // plane z - 1
     const bool more = z + 1 < z1;
-    if (more) load_plane(z + 2, pf, pv);  // in flight during the products
+    float pv = 0.f;
+    if (more) pv = load_plane(z + 2);  // in flight during the products
 
     f32x4 acc[2][2];
 #pragma unroll
@@ -186,67 +175,39 @@ __global__ __launch_bounds__(NT) void k_sg_conv(const SgConvParams p) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    if constexpr (FIRST) {
-      // K = 32 "taps" of the single input channel (27 real, 5 zero)
-      bf16x8 bo[2];
+    // K = 32 "taps" of the single input channel (27 real, 5 zero)
+    bf16x8 bo[2];
 #pragma unroll
-      for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < 2; ++n)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int k = 8 * lk + i;
-          if (k < 27) {
-            const int dz = k / 9, dy = (k / 3) % 3, dx = k % 3;  // offsets + 1
-            const int s = (s0 + dz) % 3;
-            bo[n][i] = al[s * PLANE_VOX + (wave + dy) * RX + 16 * n + li + dx];
-          } else {
-            bo[n][i] = static_cast<__bf16>(0.f);
-          }
+      for (int i = 0; i < 8; ++i) {
+        const int k = 8 * lk + i;
+        if (k < 27) {
+          const int dz = k / 9, dy = (k / 3) % 3, dx = k % 3;  // offsets + 1
+          const int s = (s0 + dz) % 3;
+          bo[n][i] = al[s * PLANE_VOX + (wave + dy) * RX + 16 * n + li + dx];
+        } else {
+          bo[n][i] = static_cast<__bf16>(0.f);
         }
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const bf16x8 a = reinterpret_cast<const bf16x8*>(wl)[(16 * m + li) * 4 + lk];
-#pragma unroll
-        for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bo[n], acc[m][n], 0, 0, 0);
       }
-    } else {
-      const bf16x8* a8 = reinterpret_cast<const bf16x8*>(al);
-      const bf16x8* w8 = reinterpret_cast<const bf16x8*>(wl);
 #pragma unroll
-      for (int t = 0; t < 27; ++t) {
-        const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-        const int s = (s0 + dz) % 3;
-        bf16x8 bo[2], ao[2];
+    for (int m = 0; m < 2; ++m) {
+      const bf16x8 a = reinterpret_cast<const bf16x8*>(wl)[(16 * m + li) * 4 + lk];
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
-          bo[n] = a8[(s * PLANE_VOX + (wave + dy) * RX + 16 * n + li + dx) * 4 + lk];
-#pragma unroll
-        for (int m = 0; m < 2; ++m) ao[m] = w8[(t * C + 16 * m + li) * 4 + lk];
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-          for (int n = 0; n < 2; ++n)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao[m], bo[n], acc[m][n], 0, 0, 0);
-      }
+      for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bo[n], acc[m][n], 0, 0, 0);
     }
 
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       const int64_t xv = x0 + 16 * n + li;
       if (yo < ny && xv < nx) {
-        const int64_t vox = ((z - p.out_z0) * ny + yo) * nx + xv;  // in out and prev
+        const int64_t vox = ((z - p.out_z0) * ny + yo) * nx + xv;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
           const int co = 16 * m + 4 * lk;
           bf16x4 o;
-          if constexpr (BWD) {
-            const bf16x4 xm = *reinterpret_cast<const bf16x4*>(p.prev + vox * C + co);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              o[r] = static_cast<__bf16>(static_cast<float>(xm[r]) > 0.f ? acc[m][n][r] : 0.f);
-          } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = static_cast<__bf16>(fmaxf(acc[m][n][r] + bias[co + r], 0.f));
-          }
+          for (int r = 0; r < 4; ++r) o[r] = static_cast<__bf16>(fmaxf(acc[m][n][r] + bias[m][r], 0.f));
           *reinterpret_cast<bf16x4*>(p.out + vox * C + co) = o;
         }
       }
@@ -254,33 +215,60 @@ __global__ __launch_bounds__(NT) void k_sg_conv(const SgConvParams p) {
 
     __syncthreads();  // every read of the ring slot about to be replaced is done
     if (more) {
-      store_plane(s0, pf, pv);  // plane z + 2 replaces plane z - 1
+      store_plane(s0, pv);  // plane z + 2 replaces plane z - 1
       __syncthreads();
     }
   }
 }
 
-// Weight-stationary 32 -> 32 layer (inference, layers 2..5).  A block of 4
-// waves (one per SIMD) owns 8 (y) x 64 (x) output voxels and marches through a
-// chunk of z planes; wave w computes rows 2w and 2w + 1, i.e. eight 16-voxel N
-// blocks.  Every lane holds its A operands of all 27 taps and both 16-channel M
-// blocks in registers for the whole chunk (216 VGPRs: the layer's weights are
-// read from memory once per block), so per tap the wave reads only its eight B
-// operands from the LDS ring and issues 16 MFMAs: half the LDS bytes per MFMA
-// of a kernel that streams the weights too.  The input planes live in a ring
-// of 3 LDS planes of 10 x 66 voxels (faces clamped; 124 KB, one block per CU);
-// the next plane's loads are issued before the current plane's products and
-// stored into the ring right after them, before the epilogue.
-// LAST: the head is three more MFMAs per N block: the layer's output and the
-// head weights each split into a high and a low bf16 part (about 16 bits of
-// each), all products but low x low.
-constexpr int WS_TY = 8, WS_TX = 64, WS_RY = WS_TY + 2, WS_RX = WS_TX + 2;
+// Weight-stationary 32 -> 32 layer: inference layers 2..5 and the training
+// passes.  A block of 4 waves (one per SIMD) owns 16 (y) x 32 (x) output voxels
+// and marches through a chunk of z planes; wave w computes rows 4w .. 4w + 3, i.e.
+// eight 16-voxel N blocks.  Every lane holds its A operands of all 27 taps and
+// both 16-channel M blocks in registers for the whole chunk (216 VGPRs: the
+// layer's weights are read from memory once per block), so per tap the wave reads
+// only its B operands from the LDS ring and issues 16 MFMAs.  The input planes
+// live in a ring of 3 LDS planes of 18 rows (faces clamped; 135 KB, one block per
+// CU); the next plane's loads are issued before the current plane's products
+// and stored into the ring right after them, before the epilogue.  Four rows of
+// 32 a wave, against two of 64, let the taps of neighbouring rows share more
+// operands (108 LDS reads a plane for 216 operands, against 144) and stage 1.20
+// instead of 1.29 voxels per output.
+//
+// A lane's operand is 16 bytes (8 channels: piece lk of a voxel's four).  A
+// 16-byte LDS read is served 16 lanes at a time (lanes 0-3, 12-15 and 20-27 of the
+// first 32, then the other 16, and so on) over 64 banks; with voxels of 64 bytes
+// laid out plainly, two lanes of such a group meet in every bank.  The pieces of
+// a voxel are therefore exchanged in pairs (piece p at place p ^ 2) where bit 2
+// of the voxel's place is set, which parts them for any first voxel.  Rows are
+// WS_RXP = 40 places, a multiple of 8, so that bit depends only on the lane and
+// the tap's x offset and every other offset stays an instruction immediate.
+//
+// MODE: WS_HIDDEN stores the activation; WS_LAST evaluates the head as three more
+// MFMAs per N block (the layer's output and the head weights each split into a
+// high and a low bf16 part, about 16 bits of each, all products but low x low);
+// WS_BWD is the backward data pass (no bias, the output multiplied by the ReLU
+// mask of p.prev, the forward activation at the output voxel).
+//
+// What bounds it: the matrix cores at the clock their power leaves (60 % of the
+// cycles busy at about 2.0 GHz: 1.23 PFLOP/s, a large library product reaches
+// 1.1 to 1.4 on this card); one wave per SIMD leaves the epilogue uncovered.
+// A hidden layer of 256 x 320 x 384 takes 1420 us (1530 with two rows of 64 a wave,
+// plain piece order and 8-byte stores), the last layer 2100 (2217), the training
+// layers of 32 patches of 32^3 57 forward and 68 backward (78 and 86 with
+// the weights streamed from LDS).
+constexpr int WS_RW = 4, WS_NB = 2;  // rows per wave, 16-voxel blocks per row
+constexpr int WS_TY = 4 * WS_RW, WS_TX = 16 * WS_NB, WS_RY = WS_TY + 2, WS_RX = WS_TX + 2;
+constexpr int WS_RXP = (WS_RX + 7) / 8 * 8;
 constexpr int WS_NT = 256;
-constexpr int WS_PLANE = WS_RY * WS_RX;
-constexpr int WS_PER = (WS_PLANE * 4 + WS_NT - 1) / WS_NT;  // 16-byte chunks per thread per plane
+constexpr int WS_PLANE = WS_RY * WS_RXP;                          // places of one staged plane
+constexpr int WS_PIECES = WS_RY * WS_RX * 4;                      // 16-byte pieces of one staged plane
+constexpr int WS_PER = (WS_PIECES + WS_NT - 1) / WS_NT;           // per thread
+constexpr int WS_HIDDEN = 0, WS_LAST = 1, WS_BWD = 2;
 
-template <bool LAST>
+template <int MODE>
 __global__ __launch_bounds__(WS_NT) void k_sg_conv_ws(const SgConvParams p) {
+  constexpr bool LAST = MODE == WS_LAST;
   __shared__ __attribute__((aligned(16))) __bf16 al[3 * WS_PLANE * C];
   __shared__ float hw[LAST ? 5 * C : 1];  // head weights (read by lane-dependent channel)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -289,66 +277,82 @@ __global__ __launch_bounds__(WS_NT) void k_sg_conv_ws(const SgConvParams p) {
     if (tid < 5 * C) hw[tid] = p.head_w[tid];
   }
   const int64_t nz = p.nz, ny = p.ny, nx = p.nx;
-  const int64_t x_tiles = (nx + WS_TX - 1) / WS_TX, y_tiles = (ny + WS_TY - 1) / WS_TY;
   int64_t b = blockIdx.x;
-  const int64_t xt = b % x_tiles;
-  b /= x_tiles;
-  const int64_t yt = b % y_tiles;
-  const int64_t zc = b / y_tiles;
+  const int64_t xt = b % p.x_tiles;
+  b /= p.x_tiles;
+  const int64_t yt = b % p.y_tiles;
+  const int64_t zc = b / p.y_tiles;
   const int64_t x0 = xt * WS_TX, y0 = yt * WS_TY;
   const int64_t z0 = p.z_lo + zc * p.zchunk;
   const int64_t z1 = (z0 + p.zchunk) < p.z_hi ? (z0 + p.zchunk) : p.z_hi;
 
-  // A operands: lane holds W[t][16 m + li][8 lk .. 8 lk + 7]
+  // the thread's staged pieces: place in the volume's plane (voxels, below 2^31
+  // since a plane of activations is 64 bytes a voxel) and in the ring's
+  int goff[WS_PER], loff[WS_PER];
+#pragma unroll
+  for (int j = 0; j < WS_PER; ++j) {
+    int c = tid + WS_NT * j;
+    if (c >= WS_PIECES) c = WS_PIECES - 1;  // the last piece again
+    const int row = (c >> 2) / WS_RX, col = (c >> 2) % WS_RX, part = c & 3;
+    goff[j] = static_cast<int>(clampi(y0 - 1 + row, ny) * nx + clampi(x0 - 1 + col, nx));
+    loff[j] = (row * WS_RXP + col) * 4 + (part ^ (((col >> 2) & 1) << 1));
+  }
+  auto load_plane = [&](int64_t zi, bf16x8 (&pf)[WS_PER]) {
+    const __bf16* src = p.in + (clampi(zi, nz) - p.in_z0) * ny * nx * C + 8 * (tid & 3);
+#pragma unroll
+    for (int j = 0; j < WS_PER; ++j)
+      pf[j] = *reinterpret_cast<const bf16x8*>(src + static_cast<int64_t>(goff[j]) * C);
+  };
+  auto store_plane = [&](int s, const bf16x8 (&pf)[WS_PER]) {
+    bf16x8* dst = reinterpret_cast<bf16x8*>(al) + s * WS_PLANE * 4;
+#pragma unroll
+    for (int j = 0; j < WS_PER; ++j)
+      if (tid + WS_NT * j < WS_PIECES) dst[loff[j]] = pf[j];
+  };
+
+  bf16x8 pf[WS_PER], pf1[WS_PER], pf2[WS_PER];
+  load_plane(z0 - 1, pf);
+  load_plane(z0, pf1);
+  load_plane(z0 + 1, pf2);
+  // Output channel of row i of M block m.  A stored layer deals the channels to
+  // the two blocks in fours, so that a lane's eight results (rows 4 lk .. 4 lk + 3
+  // of both) are the neighbouring channels 8 lk .. 8 lk + 7: one 16-byte store.
+  // The last layer keeps them in order, as the head's columns are.
+  auto channel = [](int m, int i) { return LAST ? 16 * m + i : 8 * (i >> 2) + 4 * m + (i & 3); };
+  // A operands: lane holds W[t][channel(m, li)][8 lk .. 8 lk + 7]
   bf16x8 wa[27][2];
   {
     const bf16x8* w8 = reinterpret_cast<const bf16x8*>(p.w);
 #pragma unroll
     for (int t = 0; t < 27; ++t)
 #pragma unroll
-      for (int m = 0; m < 2; ++m) wa[t][m] = w8[(t * C + 16 * m + li) * 4 + lk];
+      for (int m = 0; m < 2; ++m) wa[t][m] = w8[(t * C + channel(m, li)) * 4 + lk];
   }
   float bias[2][4];
+  if constexpr (MODE != WS_BWD) {
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) bias[m][r] = p.bias[16 * m + 4 * lk + r];
-
-  auto load_plane = [&](int64_t zi, bf16x8 (&pf)[WS_PER]) {
-    const int64_t pb = (clampi(zi, nz) - p.in_z0) * ny * nx;
-#pragma unroll
-    for (int j = 0; j < WS_PER; ++j) {
-      const int c = tid + WS_NT * j;
-      const int cc = c < WS_PLANE * 4 ? c : WS_PLANE * 4 - 1;
-      const int vi = cc >> 2, part = cc & 3;
-      const int row = vi / WS_RX, col = vi % WS_RX;
-      const int64_t g = pb + clampi(y0 - 1 + row, ny) * nx + clampi(x0 - 1 + col, nx);
-      pf[j] = reinterpret_cast<const bf16x8*>(p.in + g * C)[part];
-    }
-  };
-  auto store_plane = [&](int s, const bf16x8 (&pf)[WS_PER]) {
-#pragma unroll
-    for (int j = 0; j < WS_PER; ++j) {
-      const int c = tid + WS_NT * j;
-      if (c < WS_PLANE * 4) reinterpret_cast<bf16x8*>(al)[s * WS_PLANE * 4 + c] = pf[j];
-    }
-  };
-
-  bf16x8 pf[WS_PER];
-  load_plane(z0 - 1, pf);
+      for (int r = 0; r < 4; ++r) bias[m][r] = p.bias[channel(m, 4 * lk + r)];
+  }
   store_plane(0, pf);
-  load_plane(z0, pf);
-  store_plane(1, pf);
-  load_plane(z0 + 1, pf);
-  store_plane(2, pf);
+  store_plane(1, pf1);
+  store_plane(2, pf2);
   __syncthreads();
+  // The weights and biases arrive before the plane loop: vector memory counts
+  // loads and stores together, so a load that may still be pending at the loop's
+  // head makes every use of it wait, in every plane, for stores just issued.
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 
   // LAST: the head h = Wh x5 on the matrix cores, with Wh (rows 0..4 of a
   // 16-row A operand) split into a bf16 high and low part.  A lane's B operand
   // is its own eight channels of x5, so its K index 8 lk + i stands for
   // channel 16 (i / 4) + 4 lk + i % 4, and A's columns follow that order.
   bf16x8 wh_hi, wh_lo;
+  float hb[5];  // read here once: after the first store they would be read for every voxel
   if constexpr (LAST) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) hb[q] = p.head_b[q];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float wv = li < 5 ? hw[li * C + 16 * (i >> 2) + 4 * lk + (i & 3)] : 0.f;
@@ -359,92 +363,128 @@ __global__ __launch_bounds__(WS_NT) void k_sg_conv_ws(const SgConvParams p) {
   }
 
   const bf16x8* a8 = reinterpret_cast<const bf16x8*>(al);
+  int at[3];  // this lane's operand of the wave's first row, by the tap's x offset
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx)
+    at[dx] = (WS_RW * wave * WS_RXP + li + dx) * 4 + (lk ^ ((((li + dx) >> 2) & 1) << 1));
 #pragma unroll 1
   for (int64_t z = z0; z < z1; ++z) {
     const int s0 = static_cast<int>((z - z0) % 3);  // ring slot of plane z - 1
     const bool more = z + 1 < z1;
     if (more) load_plane(z + 2, pf);  // in flight during the products
-
-    f32x4 acc[2][8];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 8; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // this lane's operand in each ring plane (planes z - 1, z, z + 1); the tap
-    // and N-block offsets below are compile-time constants
-    const bf16x8* base[3];
-#pragma unroll
-    for (int dz = 0; dz < 3; ++dz)
-      base[dz] = a8 + ((((s0 + dz) % 3) * WS_RY + 2 * wave) * WS_RX + li) * 4 + lk;
-#pragma unroll
-    for (int t = 0; t < 27; ++t) {
-      const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-      bf16x8 bo[8];
-#pragma unroll
-      for (int n = 0; n < 8; ++n) bo[n] = base[dz][(((n >> 2) + dy) * WS_RX + 16 * (n & 3) + dx) * 4];
-#pragma unroll
-      for (int n = 0; n < 8; ++n)
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-          acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][m], bo[n], acc[m][n], 0, 0, 0);
-    }
-    // the prefetched plane goes into the ring before the epilogue, so its
-    // registers are free there
-    __syncthreads();  // every read of the ring slot about to be replaced is done
-    if (more) store_plane(s0, pf);  // plane z + 2 replaces plane z - 1
-
-    if constexpr (!LAST) {
+    // what the epilogue reads, too (clamped: of a voxel outside, nothing is stored)
+    bf16x8 xm[MODE == WS_BWD ? 8 : 1];
+    uint8_t inside[2] = {1, 1};
+    if constexpr (MODE == WS_BWD) {
 #pragma unroll
       for (int n = 0; n < 8; ++n) {
-        const int64_t yo = y0 + 2 * wave + (n >> 2), xv = x0 + 16 * (n & 3) + li;
+        const int64_t yo = clampi(y0 + WS_RW * wave + n / WS_NB, ny), xv = clampi(x0 + 16 * (n % WS_NB) + li, nx);
+        xm[n] = *reinterpret_cast<const bf16x8*>(p.prev + (((z - p.out_z0) * ny + yo) * nx + xv) * C + 8 * lk);
+      }
+    }
+    if constexpr (LAST) {
+      if (p.mask != nullptr) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int n = 4 * k + lk;
+          const int64_t yo = clampi(y0 + WS_RW * wave + n / WS_NB, ny), xv = clampi(x0 + 16 * (n % WS_NB) + li, nx);
+          inside[k] = p.mask[(z * ny + yo) * nx + xv];
+        }
+      }
+    }
+
+    // ring planes z - 1, z, z + 1; row and N-block offsets are immediates
+    const bf16x8* base[3];
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz) base[dz] = a8 + (s0 + dz) % 3 * WS_PLANE * 4;
+    // products of NB N blocks from block n0 on, every tap into one chain per result
+    auto products = [&]<int NB>(std::integral_constant<int, NB>, int n0, f32x4 (&acc)[2][NB]) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 27; ++t) {
+        const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
+        bf16x8 bo[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          bo[n] = (base[dz] + at[dx])[(((n0 + n) / WS_NB + dy) * WS_RXP + 16 * ((n0 + n) % WS_NB)) * 4];
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][m], bo[n], acc[m][n], 0, 0, 0);
+      }
+    };
+
+    if constexpr (!LAST) {
+      f32x4 acc[2][8];
+      products(std::integral_constant<int, 8>{}, 0, acc);
+      // the prefetched plane goes into the ring before the epilogue, so its
+      // registers are free there
+      __syncthreads();  // every read of the ring slot about to be replaced is done
+      if (more) store_plane(s0, pf);  // plane z + 2 replaces plane z - 1
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        const int64_t yo = y0 + WS_RW * wave + n / WS_NB, xv = x0 + 16 * (n % WS_NB) + li;
         if (yo < ny && xv < nx) {
           const int64_t vox = ((z - p.out_z0) * ny + yo) * nx + xv;
+          bf16x8 o;
 #pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            bf16x4 o;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = static_cast<__bf16>(fmaxf(acc[m][n][r] + bias[m][r], 0.f));
-            *reinterpret_cast<bf16x4*>(p.out + vox * C + 16 * m + 4 * lk) = o;
+          for (int i = 0; i < 8; ++i) {
+            const float v = acc[i >> 2][n][i & 3];
+            if constexpr (MODE == WS_BWD)
+              o[i] = static_cast<__bf16>(static_cast<float>(xm[n][i]) > 0.f ? v : 0.f);
+            else
+              o[i] = static_cast<__bf16>(fmaxf(v + bias[i >> 2][i & 3], 0.f));
           }
+          *reinterpret_cast<bf16x8*>(p.out + vox * C + 8 * lk) = o;
         }
       }
     } else {
-      // head: x5 = relu(acc + b), split like Wh into a high and a low bf16
-      // part, is the B operand as the lane holds it (the product of the two
-      // low parts, below 2^-16 of a term, is left out); D row q, column li is
-      // h[q] of voxel li (rows 0..3 in lanes 0..15, row 4 in lanes 16..31).
-      // Lanes of group lk then finish the voxels of N blocks lk and lk + 4.
-      float hs[2][5];
-#pragma unroll
-      for (int n = 0; n < 8; ++n) {
-        bf16x8 xh, xl;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float v = fmaxf(acc[i >> 2][n][i & 3] + bias[i >> 2][i & 3], 0.f);
-          xh[i] = static_cast<__bf16>(v);
-          xl[i] = static_cast<__bf16>(v - static_cast<float>(xh[i]));
-        }
-        f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_hi, xh, d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_hi, xl, d, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_lo, xh, d, 0, 0, 0);
-        float qv[5];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) qv[r] = __shfl(d[r], li);
-        qv[4] = __shfl(d[0], 16 + li);
-        if ((n & 3) == lk) {
-#pragma unroll
-          for (int q = 0; q < 5; ++q) hs[n >> 2][q] = qv[q];
-        }
-      }
+      // in two halves of four N blocks, which keeps the outputs' arithmetic out of
+      // scratch memory (with all eight blocks' sums live it spills, and every
+      // reload waits for the stores before it)
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        const int64_t yo = y0 + 2 * wave + k, xv = x0 + 16 * lk + li;
-        if (yo < ny && xv < nx) {
-          float o[5];
+        f32x4 acc[2][4];
+        products(std::integral_constant<int, 4>{}, 4 * k, acc);
+        if (k == 1) {
+          __syncthreads();  // every read of the ring slot about to be replaced is done
+          if (more) store_plane(s0, pf);  // plane z + 2 replaces plane z - 1
+        }
+        // head: x5 = relu(acc + b), split like Wh into a high and a low bf16
+        // part, is the B operand as the lane holds it (the product of the two
+        // low parts, below 2^-16 of a term, is left out); D row q, column li is
+        // h[q] of voxel li (rows 0..3 in lanes 0..15, row 4 in lanes 16..31).
+        // Lanes of group lk then finish the voxels of the half's N block lk.
+        float o[5];
 #pragma unroll
-          for (int q = 0; q < 5; ++q) o[q] = p.head_b[q] + hs[k][q];
-          head_outputs(p, o, z, yo, xv);
+        for (int n = 0; n < 4; ++n) {
+          bf16x8 xh, xl;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float v = fmaxf(acc[i >> 2][n][i & 3] + bias[i >> 2][i & 3], 0.f);
+            xh[i] = static_cast<__bf16>(v);
+            xl[i] = static_cast<__bf16>(v - static_cast<float>(xh[i]));
+          }
+          f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_hi, xh, d, 0, 0, 0);
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_hi, xl, d, 0, 0, 0);
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh_lo, xh, d, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < 5; ++q) {
+            const float qv = q < 4 ? __shfl(d[q], li) : __shfl(d[0], 16 + li);
+            o[q] = n == 0 || n == lk ? qv : o[q];
+          }
+        }
+        const int n = 4 * k + lk;
+        const int64_t yo = y0 + WS_RW * wave + n / WS_NB, xv = x0 + 16 * (n % WS_NB) + li;
+        if (yo < ny && xv < nx) {
+#pragma unroll
+          for (int q = 0; q < 5; ++q) o[q] = hb[q] + o[q];
+          head_outputs(p, o, inside[k] != 0, z, yo, xv);
         }
       }
     }
@@ -453,11 +493,15 @@ __global__ __launch_bounds__(WS_NT) void k_sg_conv_ws(const SgConvParams p) {
   }
 }
 
-template <bool LAST>
-hipError_t launch_conv_ws(const SgConvParams& p, hipStream_t stream) {
-  const int64_t blocks = ((p.nx + WS_TX - 1) / WS_TX) * ((p.ny + WS_TY - 1) / WS_TY) *
-                         ((p.z_hi - p.z_lo + p.zchunk - 1) / p.zchunk);
-  hipLaunchKernelGGL(k_sg_conv_ws<LAST>, dim3(static_cast<unsigned>(blocks)), dim3(WS_NT), 0, stream, p);
+template <int MODE>
+hipError_t launch_conv_ws(const SgConvParams& q, hipStream_t stream) {
+  SgConvParams p = q;
+  p.x_tiles = (p.nx + WS_TX - 1) / WS_TX;
+  p.y_tiles = (p.ny + WS_TY - 1) / WS_TY;
+  const int64_t planes = p.z_hi - p.z_lo;
+  p.zchunk = sg_zchunk(p.x_tiles * p.y_tiles, planes, 1, 64);
+  const int64_t blocks = p.x_tiles * p.y_tiles * ((planes + p.zchunk - 1) / p.zchunk);
+  hipLaunchKernelGGL(k_sg_conv_ws<MODE>, dim3(static_cast<unsigned>(blocks)), dim3(WS_NT), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -475,15 +519,17 @@ __global__ void k_sg_merge(const SgMergeParams p) {
   if (p.ia) p.ia[i] = p.pia[j];
 }
 
-template <bool FIRST, bool BWD = false>
-hipError_t launch_conv(const SgConvParams& p, int dtype, hipStream_t stream) {
-  const int64_t blocks = p.x_tiles * p.y_tiles * ((p.z_hi - p.z_lo + p.zchunk - 1) / p.zchunk);
+hipError_t launch_first(const SgConvParams& q, int dtype, hipStream_t stream) {
+  SgConvParams p = q;
+  p.x_tiles = (p.nx + TX - 1) / TX;
+  p.y_tiles = (p.ny + TY - 1) / TY;
+  const int64_t planes = p.z_hi - p.z_lo;
+  p.zchunk = sg_zchunk(p.x_tiles * p.y_tiles, planes, 4, 16);  // short chunks: the launch ends evenly
+  const int64_t blocks = p.x_tiles * p.y_tiles * ((planes + p.zchunk - 1) / p.zchunk);
   if (dtype == ST_DTYPE_U16)
-    hipLaunchKernelGGL((k_sg_conv<FIRST, uint16_t, BWD>), dim3(static_cast<unsigned>(blocks)), dim3(NT), 0,
-                       stream, p);
+    hipLaunchKernelGGL(k_sg_conv<uint16_t>, dim3(static_cast<unsigned>(blocks)), dim3(NT), 0, stream, p);
   else
-    hipLaunchKernelGGL((k_sg_conv<FIRST, float, BWD>), dim3(static_cast<unsigned>(blocks)), dim3(NT), 0,
-                       stream, p);
+    hipLaunchKernelGGL(k_sg_conv<float>, dim3(static_cast<unsigned>(blocks)), dim3(NT), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -496,17 +542,17 @@ hipError_t launch_sg_pack(const float* blob, __bf16* w1, __bf16* w25, hipStream_
 }
 
 hipError_t launch_sg_conv(int layer, int dtype, const SgConvParams& p, hipStream_t stream) {
-  if (layer == 1) return launch_conv<true>(p, dtype, stream);
-  if (layer == kSgLayers) return launch_conv_ws<true>(p, stream);
-  return launch_conv_ws<false>(p, stream);
+  if (layer == 1) return launch_first(p, dtype, stream);
+  if (layer == kSgLayers) return launch_conv_ws<WS_LAST>(p, stream);
+  return launch_conv_ws<WS_HIDDEN>(p, stream);
 }
 
 hipError_t launch_sg_conv_hidden(bool first, int dtype, const SgConvParams& p, hipStream_t stream) {
-  return first ? launch_conv<true>(p, dtype, stream) : launch_conv<false>(p, ST_DTYPE_F32, stream);
+  return first ? launch_first(p, dtype, stream) : launch_conv_ws<WS_HIDDEN>(p, stream);
 }
 
 hipError_t launch_sg_conv_bwd(const SgConvParams& p, hipStream_t stream) {
-  return launch_conv<false, true>(p, ST_DTYPE_F32, stream);
+  return launch_conv_ws<WS_BWD>(p, stream);
 }
 
 hipError_t launch_sg_merge(const SgMergeParams& p, hipStream_t stream) {
