@@ -553,7 +553,13 @@ int st_angles(const float* e3, const uint8_t* mask, int64_t nz, int64_t ny, int6
   p.e3 = e3; p.mask = mask; p.ha = ha; p.ia = ia; p.flags = flags;
   p.n = n; p.ny = ny; p.nx = nx; p.nrows = nz * ny;
   p.x_tiles = (nx + st::kXTile - 1) / st::kXTile;
-  p.vec_ok = 0;
+  // 16-byte accesses: the three planes of e3 and the outputs start on 16 bytes,
+  // the byte arrays on 4
+  p.vec_ok = n % 4 == 0;
+  for (const void* q : {static_cast<const void*>(e3), static_cast<const void*>(ha), static_cast<const void*>(ia)})
+    if (reinterpret_cast<uintptr_t>(q) % 16 != 0) p.vec_ok = 0;
+  for (const void* q : {static_cast<const void*>(mask), static_cast<const void*>(flags)})
+    if (reinterpret_cast<uintptr_t>(q) % 4 != 0) p.vec_ok = 0;
   for (int i = 0; i < 3; ++i) { p.center[i] = axis_center[i]; p.dir[i] = unit[i]; }
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   hipError_t e = timed("angles", stream, [&] { return st::launch_angles(p, stream); });

@@ -103,9 +103,10 @@ __device__ __forceinline__ bool fibre_angles(double vz, double vy, double vx, co
   const float ty = az * fx - ax * fz;
   const float tx = ay * fz - az * fy;
   const float uz = static_cast<float>(vz), uy = static_cast<float>(vy), ux = static_cast<float>(vx);
-  const float f_r = uz * fz + uy * fy + ux * fx;   // r * (v . e_r)
-  const float f_t = uz * tz + uy * ty + ux * tx;   // r * (v . e_t)
-  const float f_a = uz * az + uy * ay + ux * ax;   // v . a
+  // explicit fused sums, so that every kernel rounds them alike
+  const float f_r = fmaf(ux, fx, fmaf(uy, fy, uz * fz));   // r * (v . e_r)
+  const float f_t = fmaf(ux, tx, fmaf(uy, ty, uz * tz));   // r * (v . e_t)
+  const float f_a = fmaf(ux, ax, fmaf(uy, ay, uz * az));   // v . a
   const float r = __builtin_amdgcn_sqrtf(static_cast<float>(r2));
   const float den = fabsf(f_t);
   const float sg = f_t >= 0.f ? 1.f : -1.f;

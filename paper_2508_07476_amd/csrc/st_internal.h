@@ -217,7 +217,8 @@ struct AnglesParams {
   float* ia;
   uint8_t* flags;
   int64_t n, ny, nx, nrows, x_tiles;
-  int vec_ok;
+  int vec_ok;              // n a multiple of 4, e3 and the angles 16-byte, mask and flags 4-byte aligned
+  double inv_nx, inv_ny;   // reciprocals, set by launch_angles
   double center[3];
   double dir[3];
 };
