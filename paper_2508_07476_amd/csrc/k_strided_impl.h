@@ -9,6 +9,11 @@
 // one block of 2R+1 outputs ahead of its use, so every lane keeps 2R+1 loads
 // in flight; the axis position is wave-uniform (boundary reflection runs on
 // the scalar unit) and the taps are kernel arguments held in scalar registers.
+// What bounds the pass: memory up to radius 16 (48 bytes a voxel and six
+// components, 1.35 ms for 512^3, the rate of a large copy), VALU issue and the
+// window's registers above.  Waiting for each load by its exact place in the queue
+// (see `step`) took radius 24 on 512 x 1024 x 1024 from 6.6 and 6.4 ms (z, y) to 5.9
+// and 5.8, radius 32 on 190 x 226 x 250 from 264 us to 230.
 #pragma once
 #include <utility>
 
@@ -37,8 +42,7 @@ __device__ __forceinline__ void strided_block(const StridedGeo& p, const Taps& w
   const int64_t o = ot * 4 + threadIdx.y;
   if (o >= p.n_other) return;  // wave-uniform
   const int64_t x0 = xt * 64;
-  const bool active = x0 + lane < p.nx;
-  const int lx = active ? lane : static_cast<int>(p.nx - 1 - x0);  // keep loads in range
+  const int lx = x0 + lane < p.nx ? lane : static_cast<int>(p.nx - 1 - x0);  // keep accesses in range
 
   const Tin* in = static_cast<const Tin*>(p.job[job].in) + o * p.s_other + x0;
   const int64_t so = SAME ? p.s_other : p.so_other;
@@ -63,43 +67,47 @@ __device__ __forceinline__ void strided_block(const StridedGeo& p, const Taps& w
 
   // win: the 2R+1 samples of the current output; pre: the newest sample of each
   // output of the current block of W outputs, loaded one block ahead so that W
-  // loads per lane are always in flight.
+  // loads per lane are always in flight (past the chunk's last, that one again).
   double win[W];
   float pre[W];
 #pragma unroll
   for (int j = 0; j < 2 * R; ++j) win[j] = sample(j);
 #pragma unroll
-  for (int j = 0; j < W; ++j) pre[j] = sample(2 * R + j);
+  for (int j = 0; j < W; ++j) pre[j] = sample(2 * R + (j < len ? j : len - 1));
 
-  for (int tb = 0; tb < len; tb += W) {
-    auto step = [&]<int J>(std::integral_constant<int, J>) {
-      const int t = tb + J;
-      const double v = pre[J];
-      if (t + W < len) pre[J] = sample(t + W + 2 * R);  // same step of the next block
-      win[(J + 2 * R) % W] = v;
-      if (t < len) {
-        double g = 0.0, d = 0.0;
-        // the smoothing taps are symmetric and the derivative taps antisymmetric
-        // about the centre (bit for bit, as built): reading only taps 0..R keeps
-        // R + 1 of them in scalar registers instead of 2R + 1, which no longer
-        // fit at the largest radii
+  // One output.  A whole block's steps hold no branch around a load or a store:
+  // vector memory is waited for by counting what was issued after it, and across
+  // a branch that may or may not have issued something the count drops to none,
+  // so that every block would end in waiting for all its loads and stores.  A lane
+  // past the row's end carries its last column, and stores the same value there.
+  auto step = [&]<int J, bool WHOLE>(std::integral_constant<int, J>, std::bool_constant<WHOLE>, int tb) {
+    const int t = tb + J;
+    const double v = pre[J];
+    if constexpr (WHOLE) pre[J] = sample(2 * R + (t + W < len ? t + W : len - 1));  // same step of the next block
+    win[(J + 2 * R) % W] = v;
+    if (WHOLE || t < len) {
+      double g = 0.0, d = 0.0;
+      // the smoothing taps are symmetric and the derivative taps antisymmetric
+      // about the centre (bit for bit, as built): reading only taps 0..R keeps
+      // R + 1 of them in scalar registers instead of 2R + 1, which no longer
+      // fit at the largest radii
 #pragma unroll
-        for (int k = 0; k < W; ++k) {
-          const double u = win[(J + k) % W];
-          g = fma(wg.w[k <= R ? k : 2 * R - k], u, g);
-          if constexpr (WITH_D) d = fma(k <= R ? wd.w[k] : -wd.w[2 * R - k], u, d);
-        }
-        if (active) {
-          const int64_t at = static_cast<int64_t>(a0 + t) * soa + lane;
-          __builtin_nontemporal_store(static_cast<float>(g), og + at);
-          if constexpr (WITH_D) __builtin_nontemporal_store(static_cast<float>(d), od + at);
-        }
+      for (int k = 0; k < W; ++k) {
+        const double u = win[(J + k) % W];
+        g = fma(wg.w[k <= R ? k : 2 * R - k], u, g);
+        if constexpr (WITH_D) d = fma(k <= R ? wd.w[k] : -wd.w[2 * R - k], u, d);
       }
-    };
-    [&]<int... J>(std::integer_sequence<int, J...>) {
-      (step(std::integral_constant<int, J>{}), ...);
-    }(std::make_integer_sequence<int, W>{});
-  }
+      const int64_t at = static_cast<int64_t>(a0 + t) * soa + lx;
+      __builtin_nontemporal_store(static_cast<float>(g), og + at);
+      if constexpr (WITH_D) __builtin_nontemporal_store(static_cast<float>(d), od + at);
+    }
+  };
+  auto block = [&]<bool WHOLE, int... J>(std::bool_constant<WHOLE> whole, int tb, std::integer_sequence<int, J...>) {
+    (step(std::integral_constant<int, J>{}, whole, tb), ...);
+  };
+  int tb = 0;
+  for (; tb + W <= len; tb += W) block(std::true_type{}, tb, std::make_integer_sequence<int, W>{});
+  if (tb < len) block(std::false_type{}, tb, std::make_integer_sequence<int, W>{});  // what is left
 }
 
 template <int R, typename Tin, bool WITH_D, bool SAME>

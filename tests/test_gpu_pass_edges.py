@@ -1,0 +1,37 @@
+"""The path at the edges of its passes' blocks and pieces (MI355X only) against
+the FP64 oracle, with the path's tolerances: integration axes one short of, equal
+to and one past the register window (9 samples at rho radius 4) and whole
+multiples of it, rows on both sides of 64 columns, and small volumes whose axes
+are cut into many pieces."""
+
+import pytest
+import torch
+
+from test_gpu_parity import _log, _run_both
+
+from _parity import assert_parity, compare, summary
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    ((8, 9, 63), "u16", 0.5, 1.0),
+    ((10, 18, 65), "f32", 0.5, 1.0),
+    ((19, 27, 1), "u16", 0.5, 1.0),
+    ((28, 36, 130), "f32", 1.0, 1.0),
+    ((61, 40, 70), "u16", 1.0, 3.0),    # pieces of both axes
+    ((25, 24, 200), "f32", 1.75, 4.0),  # 4-row gradient tiles, a 33-sample window
+]
+
+
+@pytest.mark.parametrize("shape,dtype,sigma,rho", CASES)
+def test_pass_edges(shape, dtype, sigma, rho):
+    _log("case: pass edges", shape, dtype, sigma, rho)
+    gen = torch.Generator().manual_seed(shape[0] * 1000 + shape[2])
+    base = torch.rand(shape, generator=gen, dtype=torch.float64)
+    vol = (base * 60000).round().to(torch.int32).to(torch.uint16) if dtype == "u16" else base.to(torch.float32)
+    mask = (torch.rand(shape, generator=gen) > 0.25).to(torch.uint8)
+    center, direction = tuple((n - 1) / 2 + 0.25 for n in shape), (1.0, 0.2, -0.3)
+    g, o = _run_both(vol, sigma, rho, mask, center, direction)
+    stats = compare(g, o, shape, center, direction, mask=mask.numpy())
+    _log(summary(stats))
+    assert_parity(stats, str(shape))
