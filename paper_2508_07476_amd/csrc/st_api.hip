@@ -300,6 +300,27 @@ int check_path_buffers(const PathArgs& a) {
   return ST_OK;
 }
 
+// z pieces of the gradient pass: as many as make the launch shortest, when a piece
+// of c planes costs c + 2R (its halo planes are filtered too) and `tiles` blocks a
+// piece run on `cus` compute units.  A unit holds `fit` blocks at full rate; with k
+// of them it takes max(k / fit, 0.3 + 0.7 k / fit) of a full unit's time a plane
+// (measured on 64^3 to 300^3 volumes at radii 4, 6 and 8).  Alone on the chip the
+// fullest unit ends the launch, so k is rounded up; beside other launches the rest
+// of it is theirs.  A 64^3 volume at radius 4 takes 16 us in 32 pieces, 46 in the
+// two that pieces of 8R planes allowed; 512^3 stays whole.
+static int64_t grad_pieces(int64_t tiles, int64_t nz, int R, int64_t cus, int64_t fit, bool alone) {
+  int64_t best = 1;
+  double cost = 0.0;
+  for (int64_t m = 1; m <= nz && (m == 1 || tiles * (m - 1) < 8 * cus); m += 1 + m / 8) {
+    const int64_t c = (nz + m - 1) / m, pieces = (nz + c - 1) / c;
+    const int64_t b = tiles * pieces + (alone ? cus - 1 - (tiles * pieces + cus - 1) % cus : 0);
+    const double k = static_cast<double>(b) / static_cast<double>(cus * fit);
+    const double t = static_cast<double>(c + 2 * R) * std::max(k, 0.3 + 0.7 * k);
+    if (m == 1 || t < cost) { cost = t; best = pieces; }
+  }
+  return best;
+}
+
 void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* plan) {
   const void* volume = a.volume;
   const int64_t nz = a.nz, ny = a.ny, nx = a.nx;
@@ -347,6 +368,12 @@ void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* 
     while (waves * nchunks < shape.strided_min_waves &&
            (p.n_axis + 2 * nchunks - 1) / (2 * nchunks) >= min_chunk)
       nchunks *= 2;
+    // a launch that leaves a quarter of that target's waves unfilled takes shorter
+    // pieces, down to about the radius: a 64^3 volume at radius 12 takes 13 us in 5
+    // pieces, 21 in one; 93 x 101 x 77 at radius 8 19 in 3, 28 in one
+    const int64_t short_chunk = std::max<int64_t>(12, 7 * R / 8);
+    nchunks = static_cast<int>(std::max<int64_t>(
+        nchunks, std::min(p.n_axis / short_chunk, shape.strided_min_waves / 4 / std::max<int64_t>(waves, 1))));
     p.nchunks = nchunks;
     p.chunk = (p.n_axis + nchunks - 1) / nchunks;
     p.nchunks = static_cast<int>((p.n_axis + p.chunk - 1) / p.chunk);
@@ -368,12 +395,10 @@ void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* 
     const int64_t rows = shape.grad_rows ? shape.grad_rows : st::grad_tile_rows(ps);
     p.rows = static_cast<int>(rows);
     p.y_tiles = (ny + rows - 1) / rows;
-    // split z until there are enough waves to fill the chip (grad_min_blocks
-    // counts blocks of four waves), keeping chunks >= 8R
-    const int64_t waves_per_block = rows;  // one wave per tile row
-    int64_t nch = 1;
-    while (p.x_tiles * p.y_tiles * nch * waves_per_block < 4 * shape.grad_min_blocks && nz / (2 * nch) >= 8 * ps)
-      nch *= 2;
+    // grad_min_blocks counts blocks of four waves, four to a compute unit
+    const int64_t cus = std::max<int64_t>(1, shape.grad_min_blocks / 4);
+    const int64_t nch = grad_pieces(p.x_tiles * p.y_tiles, nz, ps, cus, rows == 8 ? 2 : ps <= 6 ? 4 : 3,
+                                    cus >= 256);
     p.chunk = (nz + nch - 1) / nch;
     p.nchunks = static_cast<int>((nz + p.chunk - 1) / p.chunk);
     p.wg = gs; p.wd = ds;

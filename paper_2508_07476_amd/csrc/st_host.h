@@ -40,12 +40,13 @@ struct PathArgs {
 };
 
 // Launch shapes: how far each pass splits its filtered axis to fill the chip.
-// The gradient pass splits z until it has at least 4 * grad_min_blocks waves
-// (blocks of four waves' worth); the strided passes split until they have at
-// least strided_min_waves waves (in both cases only while the pieces stay long
-// against the filter radius).  Every gradient piece re-reads 2R halo planes, so
-// the split stops at four waves per SIMD: a 512^3 volume's x-y tiles already
-// fill the chip.  A batch of concurrent chains uses a quarter of both targets.
+// grad_min_blocks: blocks of four gradient waves that fill the compute units the
+// launch has for itself (1024: the chip); the pass splits z where that shortens
+// the launch (every piece filters 2R halo planes again, so a 512^3 volume, whose
+// x-y tiles fill the chip, stays whole).  The strided passes split until they
+// have at least strided_min_waves waves while the pieces stay long against the
+// filter radius, and down to pieces of about the radius until they have a quarter
+// of that.  A batch of concurrent chains uses a quarter of both targets.
 // Tile shapes: grad_rows (output rows per gradient block) and xfinal_lanes
 // (lanes per row segment of the final pass); 0 takes the library's default for
 // the radius and width, other values must be compiled for the radius
