@@ -9,47 +9,53 @@
 namespace st {
 namespace {
 
-constexpr int kFlagWaves = 4;   // waves per block of the flag pass
 constexpr int kRowThreads = 128;  // threads per crop row (gather, merge)
 
-__device__ __forceinline__ void raise_flag(int* f) {
-  if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-    __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__global__ __launch_bounds__(256) void k_sg_fill_zero(int* p, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// One wave per 64-voxel row segment; segments start at multiples of 64, so a
-// segment lies in one tile of edge 64 or 128 and in two of edge 32.
-__global__ __launch_bounds__(64 * kFlagWaves) void k_sg_tile_flags(const SgTileFlagParams p) {
-  const int lane = threadIdx.x & 63;
-  const int64_t segs = (p.nx + 63) >> 6;
-  const int64_t g = static_cast<int64_t>(blockIdx.x) * kFlagWaves + (threadIdx.x >> 6);
-  if (g >= p.nz * p.ny * segs) return;  // uniform across the wave
-  const int64_t row = g / segs, seg = g - row * segs;
-  const int64_t z = row / p.ny, y = row - z * p.ny;
-  const int64_t x = (seg << 6) + lane;
-  bool low = false;
-  if (x < p.nx) {
-    const int64_t i = row * p.nx + x;
-    low = (p.mask == nullptr || p.mask[i] != 0) && p.conf[i] < p.threshold;
-  }
-  const uint64_t b = __ballot(low);
-  if (b == 0) return;
+// Clears the flags of edges 64 and 128.
+__global__ __launch_bounds__(256) void k_sg_clear_flags(const SgTileFlagParams p) {
+  int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
 #pragma unroll
-  for (int k = 0; k < kSgTileEdges; ++k) {
-    const int s = 5 + k;
-    const int64_t tyn = (p.ny + (int64_t(1) << s) - 1) >> s, txn = (p.nx + (int64_t(1) << s) - 1) >> s;
-    int* f = p.flags[k] + ((z >> s) * tyn + (y >> s)) * txn;
-    if (k == 0) {
-      if (lane == 0 && (b & 0xffffffffull)) raise_flag(f + 2 * seg);
-      if (lane == 32 && (b >> 32)) raise_flag(f + 2 * seg + 1);
-    } else if (lane == 0) {
-      raise_flag(f + (seg >> (k - 1)));
+  for (int k = 1; k < kSgTileEdges; ++k) {
+    if (i >= 0 && i < p.tiles[k]) p.flags[k][i] = 0;
+    i -= p.tiles[k];
+  }
+}
+
+// One block per tile of edge 32 (a thread per column of 32 planes): it alone writes
+// the tile's flag, and raises those of the tiles of edge 64 and 128 around it.
+// Reads bound it: 192 x 256 x 250 takes 37 us; a wave per 64-voxel row segment, all
+// raising the flags of all three grids, took 217.
+constexpr int kFlagEdge = 32;
+__global__ __launch_bounds__(kFlagEdge * kFlagEdge) void k_sg_tile_flags(const SgTileFlagParams p) {
+  const int64_t tyn = (p.ny + kFlagEdge - 1) / kFlagEdge, txn = (p.nx + kFlagEdge - 1) / kFlagEdge;
+  const int64_t t = blockIdx.x, tx = t % txn, ty = t / txn % tyn, tz = t / txn / tyn;
+  const int64_t x = tx * kFlagEdge + threadIdx.x % kFlagEdge, y = ty * kFlagEdge + threadIdx.x / kFlagEdge;
+  bool low = false;
+  if (x < p.nx && y < p.ny) {
+    const int64_t z0 = tz * kFlagEdge, plane = p.ny * p.nx, col = y * p.nx + x;
+    constexpr int BATCH = 8;  // planes whose loads are in flight together
+    for (int64_t z = z0; z < z0 + kFlagEdge && z < p.nz; z += BATCH) {
+      float conf[BATCH];
+      uint8_t inside[BATCH];
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) {
+        const int64_t i = (z + k < p.nz ? z + k : p.nz - 1) * plane + col;  // past the end: the last again
+        conf[k] = p.conf[i];
+        inside[k] = p.mask == nullptr ? 1 : p.mask[i];
+      }
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) low |= inside[k] != 0 && conf[k] < p.threshold;
     }
+  }
+  const int any = __syncthreads_or(low);
+  if (threadIdx.x >= kSgTileEdges) return;
+  const int k = static_cast<int>(threadIdx.x), s = 5 + k;
+  if (k == 0) {
+    p.flags[0][t] = any;
+  } else if (any) {
+    const int64_t kyn = (p.ny + (int64_t(1) << s) - 1) >> s, kxn = (p.nx + (int64_t(1) << s) - 1) >> s;
+    __hip_atomic_store(p.flags[k] + ((tz >> k) * kyn + (ty >> k)) * kxn + (tx >> k), 1, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -101,15 +107,14 @@ bool fits_grid(int64_t blocks) { return blocks >= 1 && blocks <= 0x7fffffff; }
 }  // namespace
 
 hipError_t launch_sg_tile_flags(const SgTileFlagParams& p, hipStream_t stream) {
-  for (int k = 0; k < kSgTileEdges; ++k) {
-    if (!fits_grid((p.tiles[k] + 255) / 256)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sg_fill_zero, dim3(static_cast<unsigned>((p.tiles[k] + 255) / 256)), dim3(256), 0, stream,
-                       p.flags[k], p.tiles[k]);
-  }
-  const int64_t waves = p.nz * p.ny * ((p.nx + 63) >> 6);
-  const int64_t blocks = (waves + kFlagWaves - 1) / kFlagWaves;
-  if (!fits_grid(blocks)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_sg_tile_flags, dim3(static_cast<unsigned>(blocks)), dim3(64 * kFlagWaves), 0, stream, p);
+  int64_t tiles = 0;
+  for (int k = 1; k < kSgTileEdges; ++k) tiles += p.tiles[k];
+  if (!fits_grid((tiles + 255) / 256) || !fits_grid(p.tiles[0])) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_sg_clear_flags, dim3(static_cast<unsigned>((tiles + 255) / 256)), dim3(256), 0, stream, p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sg_tile_flags, dim3(static_cast<unsigned>(p.tiles[0])), dim3(kFlagEdge * kFlagEdge), 0, stream,
+                     p);
   return hipGetLastError();
 }
 
