@@ -43,10 +43,21 @@ struct SgConvParams {
   // planes z_lo - 1 .. z_hi, clamped to the volume, must be there), `out` and
   // `prev` from out_z0 on.  The raw volume and the final outputs are whole.
   int64_t z_lo, z_hi, in_z0, out_z0;
+  // Where the mask holds, by cells of kSgCell^3 voxels ([z][y][x] bytes, nonzero:
+  // a masked voxel in the cell), or NULL (every plane of every tile is computed).
+  // A layer computes the planes of its tiles that lie within `reach` voxels (the
+  // layers still to come) of a marked cell.  build_cells: the launch of layer 1
+  // fills the cells from the mask first.
+  uint8_t* cells;
+  int build_cells;
+  int reach;
   int has_axis;
   double center[3];
   double dir[3];
 };
+
+constexpr int kSgCell = 4;
+constexpr int64_t sg_cells(int64_t n) { return (n + kSgCell - 1) / kSgCell; }
 
 // Merge of a run of voxels [begin, begin + count) of the volume (n voxels):
 // where the mask holds and the confidence is below the threshold, the outputs

@@ -394,7 +394,12 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
   const size_t confb = own_conf ? align256(N * 4) : 0;
   TileGrids grids(nz, ny, nx);
   const size_t flagb = fallback ? align256(grids.total * 4) : 0;
-  const size_t total = w1b + w25b + confb + flagb;
+  // with a mask, the cells that say which tiles the network is needed in; not
+  // below 2^20 voxels, where marking them costs about what it saves
+  const bool use_cells = mask != nullptr && n >= (int64_t(1) << 20);
+  const size_t cellb =
+      use_cells ? align256(static_cast<size_t>(st::sg_cells(nz) * st::sg_cells(ny) * st::sg_cells(nx))) : 0;
+  const size_t total = w1b + w25b + confb + flagb + cellb;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   // the activations (the bulk) serve a whole-volume fallback as its scratch
   char* acts = nullptr;
@@ -417,6 +422,7 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
   __bf16* w25 = reinterpret_cast<__bf16*>(take(w25b));
   float* conf = own_conf ? reinterpret_cast<float*>(take(confb)) : confidence;
   int* dflags = reinterpret_cast<int*>(take(flagb));
+  uint8_t* cells = reinterpret_cast<uint8_t*>(take(cellb));
 
   const float* blob = static_cast<const float*>(weights);
   const char* stage = "surrogate_pack";
@@ -456,6 +462,9 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
         p.in_z0 = in_z0;
         p.out = layer < st::kSgLayers ? bufs[(layer - 1) & 1] : nullptr;
         p.out_z0 = p.z_lo;
+        p.cells = cells;
+        p.build_cells = za == 0;
+        p.reach = static_cast<int>(g);
         p.w = layer >= 2 ? w25 + static_cast<size_t>(layer - 2) * 27 * C * C : nullptr;
         p.bias = layer == 1 ? blob + st::kSgOffB1
                             : blob + st::kSgOffW2 + (layer - 2) * st::kSgLayerStride + C * C * 27;
