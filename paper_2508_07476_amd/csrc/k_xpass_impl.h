@@ -196,7 +196,7 @@ __device__ __forceinline__ void xfinal_block(const XFinalGeo& p, const Taps& w, 
 #pragma unroll
   for (int c = 0; c < 6; ++c) seg[c] = &lds[c][sub * LR];
 
-  // mask bytes of the lane's voxels, fetched first so the loads overlap the filtering
+  // mask bytes of the lane's voxels
   uint32_t inside_bits = 0xFu;
   if (p.mask != nullptr) {
     inside_bits = 0u;
@@ -206,93 +206,109 @@ __device__ __forceinline__ void xfinal_block(const XFinalGeo& p, const Taps& w, 
       inside_bits |= (p.mask[base + xr] != 0 ? 1u : 0u) << v;
     }
   }
-  double acc[6][kXVec];
-  if constexpr (TL == 64) {
-    // The six float32 rows' bytes hold three float64 rows: stage and integrate
-    // the components in two halves of three, widening every staged value once
-    // (it lies in the windows of up to R / 2 + 1 lanes).
-    constexpr int NS = stage_slots(R, TL);
-    double* drow = reinterpret_cast<double*>(&lds[0][0]);
-    int idx[NS];
-    stage_index<R, TL>(idx, x0, p.nx, l);
-    const int64_t sbase = rr * p.pitch;  // integrated products: workspace rows
+  uint32_t flag_word = 0u;  // the lane's flag bytes, voxel v in byte v
+  const int64_t n = p.n;
+  // a wave without a voxel of the mask only writes what lies outside it: a heart's
+  // wall leaves an eighth to a half of the segments so
+  if (__any(inside_bits != 0u)) {
+    double acc[6][kXVec];
+    if constexpr (TL == 64) {
+      // The six float32 rows' bytes hold three float64 rows: stage and integrate
+      // the components in two halves of three, widening every staged value once
+      // (it lies in the windows of up to R / 2 + 1 lanes).
+      constexpr int NS = stage_slots(R, TL);
+      double* drow = reinterpret_cast<double*>(&lds[0][0]);
+      int idx[NS];
+      stage_index<R, TL>(idx, x0, p.nx, l);
+      const int64_t sbase = rr * p.pitch;  // integrated products: workspace rows
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float v[3][NS];
+      for (int h = 0; h < 2; ++h) {
+        float v[3][NS];
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int j = 0; j < NS; ++j) v[c][j] = p.s[3 * h + c][sbase + idx[j]];
-      if (h == 1) __syncthreads();  // the first half's windows are read
+          for (int j = 0; j < NS; ++j) v[c][j] = p.s[3 * h + c][sbase + idx[j]];
+        if (h == 1) __syncthreads();  // the first half's windows are read
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int j = 0; j < NS; ++j) drow[c * LR + l + TL * j] = static_cast<double>(v[c][j]);
+          for (int j = 0; j < NS; ++j) drow[c * LR + l + TL * j] = static_cast<double>(v[c][j]);
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 3; ++c) conv4_f64<R, true>(drow + c * LR, l, w, acc[3 * h + c]);
+      }
+    } else {
+      int idx[stage_slots(R, TL)];
+      stage_index<R, TL>(idx, x0, p.nx, l);
+      const int64_t sbase = rr * p.pitch;  // integrated products: workspace rows
+#pragma unroll
+      for (int c = 0; c < 6; ++c) stage_row<R, TL>(seg[c], p.s[c] + sbase, idx, l);
       __syncthreads();
 #pragma unroll
-      for (int c = 0; c < 3; ++c) conv4_f64<R, true>(drow + c * LR, l, w, acc[3 * h + c]);
+      for (int c = 0; c < 6; ++c) conv4<R, true>(seg[c], l, w, acc[c]);
     }
-  } else {
-    int idx[stage_slots(R, TL)];
-    stage_index<R, TL>(idx, x0, p.nx, l);
-    const int64_t sbase = rr * p.pitch;  // integrated products: workspace rows
-#pragma unroll
-    for (int c = 0; c < 6; ++c) stage_row<R, TL>(seg[c], p.s[c] + sbase, idx, l);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 6; ++c) conv4<R, true>(seg[c], l, w, acc[c]);
-  }
-  __syncthreads();  // every window read before the rows receive results
+    __syncthreads();  // every window read before the rows receive results
 
-  // (z, y) of the lane's row; with several rows per wave the wave's first row
-  // is divided once and stepped (at most 64 / TL - 1 steps)
-  double pz, py;
-  if constexpr (TL == 64) {
-    pz = static_cast<double>(row / p.ny);
-    py = static_cast<double>(row % p.ny);
-  } else {
-    int64_t pzi = row0 / p.ny, pyi = row0 % p.ny + sub;
-    while (pyi >= p.ny) { pyi -= p.ny; ++pzi; }
-    pz = static_cast<double>(pzi);
-    py = static_cast<double>(pyi);
-  }
-  const int64_t n = p.n;
-  uint32_t flag_word = 0u;  // the lane's flag bytes, voxel v in byte v
+    // (z, y) of the lane's row; with several rows per wave the wave's first row
+    // is divided once and stepped (at most 64 / TL - 1 steps)
+    double pz, py;
+    if constexpr (TL == 64) {
+      pz = static_cast<double>(row / p.ny);
+      py = static_cast<double>(row % p.ny);
+    } else {
+      int64_t pzi = row0 / p.ny, pyi = row0 % p.ny + sub;
+      while (pyi >= p.ny) { pyi -= p.ny; ++pzi; }
+      pz = static_cast<double>(pzi);
+      py = static_cast<double>(pyi);
+    }
 #pragma unroll 1
-  for (int v = 0; v < kXVec; ++v) {
-    const int xv = x + v;
-    const bool inside = (inside_bits >> v) & 1u;
-    double s6[6];
+    for (int v = 0; v < kXVec; ++v) {
+      const int xv = x + v;
+      const bool inside = (inside_bits >> v) & 1u;
+      double s6[6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {  // voxel v's tensor is always in slot 0: rotate the rest down
-      s6[c] = acc[c][0];
-      acc[c][0] = acc[c][1];
-      acc[c][1] = acc[c][2];
-      acc[c][2] = acc[c][3];
-    }
-    float res[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float l1 = 0.f, l2 = 0.f, l3 = 0.f;
-    uint32_t fl = ST_FLAG_OUTSIDE_MASK;
-    if (inside) {
-      EigOut o;
-      eig_smallest(s6, o);
-      res[0] = static_cast<float>(o.vz);
-      res[1] = static_cast<float>(o.vy);
-      res[2] = static_cast<float>(o.vx);
-      res[3] = o.fa;
-      l1 = o.l1; l2 = o.l2; l3 = o.l3;
-      fl = o.degenerate ? ST_FLAG_DEGENERATE : 0u;
-      if (p.has_axis && fibre_angles(o.vz, o.vy, o.vx, p.center, p.dir, pz, py,
-                                     static_cast<double>(xv), res[4], res[5]))
-        fl |= ST_FLAG_ON_AXIS;
-    }
+      for (int c = 0; c < 6; ++c) {  // voxel v's tensor is always in slot 0: rotate the rest down
+        s6[c] = acc[c][0];
+        acc[c][0] = acc[c][1];
+        acc[c][1] = acc[c][2];
+        acc[c][2] = acc[c][3];
+      }
+      float res[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      float l1 = 0.f, l2 = 0.f, l3 = 0.f;
+      uint32_t fl = ST_FLAG_OUTSIDE_MASK;
+      if (inside) {
+        EigOut o;
+        eig_smallest(s6, o);
+        res[0] = static_cast<float>(o.vz);
+        res[1] = static_cast<float>(o.vy);
+        res[2] = static_cast<float>(o.vx);
+        res[3] = o.fa;
+        l1 = o.l1; l2 = o.l2; l3 = o.l3;
+        fl = o.degenerate ? ST_FLAG_DEGENERATE : 0u;
+        if (p.has_axis && fibre_angles(o.vz, o.vy, o.vx, p.center, p.dir, pz, py,
+                                       static_cast<double>(xv), res[4], res[5]))
+          fl |= ST_FLAG_ON_AXIS;
+      }
 #pragma unroll
-    for (int q = 0; q < 6; ++q) seg[q][kXVec * l + v] = res[q];
-    if (row_ok && xv < nxi && p.evals) {  // optional output: scalar stores
-      const int64_t i = base + xv;
-      p.evals[i] = l1; p.evals[n + i] = l2; p.evals[2 * n + i] = l3;
+      for (int q = 0; q < 6; ++q) seg[q][kXVec * l + v] = res[q];
+      if (row_ok && xv < nxi && p.evals) {  // optional output: scalar stores
+        const int64_t i = base + xv;
+        p.evals[i] = l1; p.evals[n + i] = l2; p.evals[2 * n + i] = l3;
+      }
+      flag_word |= (fl & 0xffu) << (8 * v);
     }
-    flag_word |= (fl & 0xffu) << (8 * v);
+  } else {  // wave-uniform
+#pragma unroll
+    for (int q = 0; q < 6; ++q) *reinterpret_cast<float4*>(&seg[q][kXVec * l]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    flag_word = 0x01010101u * ST_FLAG_OUTSIDE_MASK;
+    if (p.evals && row_ok) {
+#pragma unroll
+      for (int v = 0; v < kXVec; ++v)
+        if (x + v < nxi) {
+          const int64_t i = base + x + v;
+          p.evals[i] = 0.f; p.evals[n + i] = 0.f; p.evals[2 * n + i] = 0.f;
+        }
+    }
   }
   if (p.flags != nullptr && row_ok && x < nxi) {
     // the lane's four flag bytes as one aligned 32-bit store where they are
