@@ -35,7 +35,8 @@ namespace st {
 namespace {
 
 // Block `blk` of the gradient pass over the volume described by p (taps wg, wd).
-template <int R, typename Tin, int TY>
+// MASKED: only the runs of marked cells along z are computed (p.cells).
+template <int R, typename Tin, int TY, bool MASKED = false>
 __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& wg, const Taps& wd, int64_t blk) {
   constexpr int W = 2 * R + 1;
   constexpr int TX = kGradTX;
@@ -53,7 +54,14 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
   // XCD a contiguous run of tiles so that tiles sharing halo rows meet in one L2.
   const int64_t nblk = p.x_tiles * p.y_tiles * p.nchunks;
   int64_t b = blk;
-  if (nblk % 8 == 0) b = (b % 8) * (nblk / 8) + b / 8;
+  if constexpr (MASKED) {
+    // runs of four tile rows, dealt to the XCDs in turn: with one long run each, an
+    // XCD at the edge of the mask would end early
+    const int64_t run = 4 * p.x_tiles, whole = nblk / (8 * run) * (8 * run);
+    if (b < whole) b = (b / 8 / run * 8 + b % 8) * run + b / 8 % run;
+  } else if (nblk % 8 == 0) {
+    b = (b % 8) * (nblk / 8) + b / 8;
+  }
   const int64_t xt = b % p.x_tiles;
   b /= p.x_tiles;
   const int64_t yt = b % p.y_tiles;
@@ -63,8 +71,8 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
   // z positions fit in 32 bits (each size < 2^31): their compares and the
   // reflection stay on the scalar unit; element offsets are 64-bit
   const int nzi = static_cast<int>(nz);
-  const int z0 = chunk_id * static_cast<int>(p.chunk);
-  const int len = (nzi - z0) < p.chunk ? (nzi - z0) : static_cast<int>(p.chunk);
+  const int c0 = chunk_id * static_cast<int>(p.chunk);
+  const int clen = (nzi - c0) < p.chunk ? (nzi - c0) : static_cast<int>(p.chunk);
   const int64_t plane = ny * nx;  // < 2^31 (checked by the host)
   const Tin* vol = static_cast<const Tin*>(p.vol);
 
@@ -79,116 +87,130 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
     const int gx = reflect_lane(static_cast<int>(x0) - R + col, static_cast<int>(nx));
     off[j] = gy * static_cast<int>(nx) + gx;
   }
-  // the input plane in flight, as loaded: a conversion here would wait for it
-  Tin pf[NSTAGE];
-  auto fetch = [&](int zi) {  // loads of input plane zi into pf
-    const Tin* src = vol + static_cast<int64_t>(reflect_lane(zi, nzi)) * plane;
+  auto run = [&](int z0, int len) {  // output planes z0 .. z0 + len - 1
+    // the input plane in flight, as loaded: a conversion here would wait for it
+    Tin pf[NSTAGE];
+    auto fetch = [&](int zi) {  // loads of input plane zi into pf
+      const Tin* src = vol + static_cast<int64_t>(reflect_lane(zi, nzi)) * plane;
 #pragma unroll
-    for (int j = 0; j < NSTAGE; ++j) pf[j] = src[off[j]];  // halo re-read by neighbours: keep cached
-  };
+      for (int j = 0; j < NSTAGE; ++j) pf[j] = src[off[j]];  // halo re-read by neighbours: keep cached
+    };
 
-  auto stage = [&](int j) {  // the fetched plane into step j's buffer
-    float* rb = raw[j & 1];
+    auto stage = [&](int j) {  // the fetched plane into step j's buffer
+      float* rb = raw[j & 1];
 #pragma unroll
-    for (int t = 0; t < NSTAGE; ++t) {
-      const int s = tid + NT * t;
-      if (s < RX * RY) rb[s] = static_cast<float>(pf[t]);
-    }
-  };
-
-  // Filter plane step j (staged) along y then x: the three partial results of
-  // this thread's column.  Then stage plane step j + 1, whose loads have been in
-  // flight since the step before, and issue those of step j + 2: the wait for
-  // loads also waits for the products stored before them, which by then had the
-  // two filters' time to leave.
-  auto filter_plane = [&](int j, int nplanes, double& a, double& bq, double& c) {
-    const float* rb = raw[j & 1];
-    __syncthreads();
-    // y filter of the wave's own row (columns tx and tx + 64 of RX): only this
-    // wave reads it, so no block barrier separates it from the x filter
-#pragma unroll
-    for (int q = 0; q < (RX + 63) / 64; ++q) {
-      const int col = tx + 64 * q;
-      if (col < RX) {
-        double g = 0.0, d = 0.0;
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-          const double v = rb[(ty + k) * RX + col];
-          g = fma(tg(k), v, g);
-          d = fma(wd.w[k], v, d);
-        }
-        yb[0][ty * RX + col] = g;
-        yb[1][ty * RX + col] = d;
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    double ga = 0.0, gb = 0.0, dc = 0.0;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      const double u = yb[0][ty * RX + tx + k];
-      const double w = yb[1][ty * RX + tx + k];
-      ga = fma(tg(k), u, ga);
-      dc = fma(wd.w[k], u, dc);
-      gb = fma(tg(k), w, gb);
-    }
-    // materialise the three results here: otherwise the compiler sinks these
-    // sums towards their use in the z filter and keeps every LDS value alive
-    asm volatile("" : "+v"(ga), "+v"(gb), "+v"(dc));
-    if (j + 1 < nplanes) {
-      stage(j + 1);
-      if (j + 2 < nplanes) fetch(z0 - R + j + 2);
-    }
-    a = ga;   // Gx Gy V   -> Dz gives g_z
-    bq = gb;  // Gx Dy V   -> Gz gives g_y
-    c = dc;   // Dx Gy V   -> Gz gives g_x
-  };
-
-  const bool active = (x0 + tx < nx) && (y0 + ty < ny);
-  const int64_t out_col = (y0 + ty) * p.opitch + (x0 + tx);
-  const int64_t out_plane = ny * p.opitch;
-
-  // z windows: slot (j + k) mod W of w* holds the column's partial results of
-  // input plane j - 2R + k at plane step j; the plane loop is expanded W times
-  // so that every slot index is static (no register moves)
-  double wa[W], wb[W], wc[W];
-  const int nplanes = len + 2 * R;  // at least 3
-  fetch(z0 - R);
-  stage(0);
-  fetch(z0 - R + 1);
-#pragma unroll 1
-  for (int jb = 0; jb < nplanes; jb += W) {  // block-uniform trip count
-    auto step = [&]<int J>(std::integral_constant<int, J>) {
-      const int j = jb + J;
-      if (j < nplanes) {
-        double a, bq, c;
-        filter_plane(j, nplanes, a, bq, c);
-        constexpr int S = (J + 2 * R) % W;
-        wa[S] = a;
-        wb[S] = bq;
-        wc[S] = c;
-        if (j >= 2 * R && active) {
-          double gz = 0.0, gy = 0.0, gx = 0.0;
-#pragma unroll
-          for (int k = 0; k < W; ++k) {
-            gz = fma(wd.w[k], wa[(J + k) % W], gz);
-            gy = fma(tg(k), wb[(J + k) % W], gy);
-            gx = fma(tg(k), wc[(J + k) % W], gx);
-          }
-          const int64_t i = static_cast<int64_t>(z0 + j - 2 * R) * out_plane + out_col;
-          __builtin_nontemporal_store(static_cast<float>(gz * gz), p.prod[0] + i);
-          __builtin_nontemporal_store(static_cast<float>(gz * gy), p.prod[1] + i);
-          __builtin_nontemporal_store(static_cast<float>(gz * gx), p.prod[2] + i);
-          __builtin_nontemporal_store(static_cast<float>(gy * gy), p.prod[3] + i);
-          __builtin_nontemporal_store(static_cast<float>(gy * gx), p.prod[4] + i);
-          __builtin_nontemporal_store(static_cast<float>(gx * gx), p.prod[5] + i);
-        }
+      for (int t = 0; t < NSTAGE; ++t) {
+        const int s = tid + NT * t;
+        if (s < RX * RY) rb[s] = static_cast<float>(pf[t]);
       }
     };
-    [&]<int... J>(std::integer_sequence<int, J...>) {
-      (step(std::integral_constant<int, J>{}), ...);
-    }(std::make_integer_sequence<int, W>{});
+
+    // Filter plane step j (staged) along y then x: the three partial results of
+    // this thread's column.  Then stage plane step j + 1, whose loads have been in
+    // flight since the step before, and issue those of step j + 2: the wait for
+    // loads also waits for the products stored before them, which by then had the
+    // two filters' time to leave.
+    auto filter_plane = [&](int j, int nplanes, double& a, double& bq, double& c) {
+      const float* rb = raw[j & 1];
+      __syncthreads();
+      // y filter of the wave's own row (columns tx and tx + 64 of RX): only this
+      // wave reads it, so no block barrier separates it from the x filter
+#pragma unroll
+      for (int q = 0; q < (RX + 63) / 64; ++q) {
+        const int col = tx + 64 * q;
+        if (col < RX) {
+          double g = 0.0, d = 0.0;
+#pragma unroll
+          for (int k = 0; k < W; ++k) {
+            const double v = rb[(ty + k) * RX + col];
+            g = fma(tg(k), v, g);
+            d = fma(wd.w[k], v, d);
+          }
+          yb[0][ty * RX + col] = g;
+          yb[1][ty * RX + col] = d;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      double ga = 0.0, gb = 0.0, dc = 0.0;
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        const double u = yb[0][ty * RX + tx + k];
+        const double w = yb[1][ty * RX + tx + k];
+        ga = fma(tg(k), u, ga);
+        dc = fma(wd.w[k], u, dc);
+        gb = fma(tg(k), w, gb);
+      }
+      // materialise the three results here: otherwise the compiler sinks these
+      // sums towards their use in the z filter and keeps every LDS value alive
+      asm volatile("" : "+v"(ga), "+v"(gb), "+v"(dc));
+      if (j + 1 < nplanes) {
+        stage(j + 1);
+        if (j + 2 < nplanes) fetch(z0 - R + j + 2);
+      }
+      a = ga;   // Gx Gy V   -> Dz gives g_z
+      bq = gb;  // Gx Dy V   -> Gz gives g_y
+      c = dc;   // Dx Gy V   -> Gz gives g_x
+    };
+
+    const bool active = (x0 + tx < nx) && (y0 + ty < ny);
+    const int64_t out_col = (y0 + ty) * p.opitch + (x0 + tx);
+    const int64_t out_plane = ny * p.opitch;
+
+    // z windows: slot (j + k) mod W of w* holds the column's partial results of
+    // input plane j - 2R + k at plane step j; the plane loop is expanded W times
+    // so that every slot index is static (no register moves)
+    double wa[W], wb[W], wc[W];
+    const int nplanes = len + 2 * R;  // at least 3
+    fetch(z0 - R);
+    stage(0);
+    fetch(z0 - R + 1);
+#pragma unroll 1
+    for (int jb = 0; jb < nplanes; jb += W) {  // block-uniform trip count
+      auto step = [&]<int J>(std::integral_constant<int, J>) {
+        const int j = jb + J;
+        if (j < nplanes) {
+          double a, bq, c;
+          filter_plane(j, nplanes, a, bq, c);
+          constexpr int S = (J + 2 * R) % W;
+          wa[S] = a;
+          wb[S] = bq;
+          wc[S] = c;
+          if (j >= 2 * R && active) {
+            double gz = 0.0, gy = 0.0, gx = 0.0;
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+              gz = fma(wd.w[k], wa[(J + k) % W], gz);
+              gy = fma(tg(k), wb[(J + k) % W], gy);
+              gx = fma(tg(k), wc[(J + k) % W], gx);
+            }
+            const int64_t i = static_cast<int64_t>(z0 + j - 2 * R) * out_plane + out_col;
+            __builtin_nontemporal_store(static_cast<float>(gz * gz), p.prod[0] + i);
+            __builtin_nontemporal_store(static_cast<float>(gz * gy), p.prod[1] + i);
+            __builtin_nontemporal_store(static_cast<float>(gz * gx), p.prod[2] + i);
+            __builtin_nontemporal_store(static_cast<float>(gy * gy), p.prod[3] + i);
+            __builtin_nontemporal_store(static_cast<float>(gy * gx), p.prod[4] + i);
+            __builtin_nontemporal_store(static_cast<float>(gx * gx), p.prod[5] + i);
+          }
+        }
+      };
+      [&]<int... J>(std::integer_sequence<int, J...>) {
+        (step(std::integral_constant<int, J>{}), ...);
+      }(std::make_integer_sequence<int, W>{});
+    }
+  };
+  if constexpr (MASKED) {
+    const int64_t cxn = p.x_tiles, cyn = (ny + 7) / 8;  // cells are 64 columns wide, 8 rows high
+    CellRuns runs(p.cells + y0 / 8 * cxn + xt, cyn * cxn, c0, clen);
+    int ra, rlen;
+#pragma unroll 1
+    while (runs.next(ra, rlen)) {  // the same in every wave of the block
+      run(ra, rlen);
+      __syncthreads();  // the next run's first planes overwrite this one's last
+    }
+  } else {
+    run(c0, clen);
   }
 }
 
@@ -196,6 +218,92 @@ template <int R, typename Tin, int TY = grad_tile_rows(R)>
 __global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 ? 4 : 1)))
 void k_grad_fused(const GradFusedParams p) {
   grad_fused_block<R, Tin, TY>(p, p.wg, p.wd, blockIdx.x);
+}
+
+// With a wall mask that fills 0.49 of 512^3 u16 (sigma 1.5, rho 4) the gradient pass
+// takes 1.18 ms instead of 1.25 (every tile is resident at once, so the fullest
+// column of blocks still ends it) and 0.04 for the cells, the integrations 1.10 and
+// 1.02 instead of 1.38 and 1.35; 400 x 640 x 600 (sigma 2, rho 6): 1.56 instead of
+// 2.01, 1.37 and 1.21 instead of 1.88 and 1.84.
+template <int R, typename Tin, int TY = grad_tile_rows(R)>
+__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 ? 4 : 1)))
+void k_grad_masked(const GradFusedParams p) {
+  grad_fused_block<R, Tin, TY, true>(p, p.wg, p.wd, blockIdx.x);
+}
+
+// The mask by cells of 8^3 voxels: a thread per plane of a cell (eight rows of eight
+// bytes, in flight together), a block for 32 neighbouring cells.
+__global__ __launch_bounds__(256) void k_mask_cells(const uint8_t* mask, int64_t nz, int64_t ny, int64_t nx, int64_t cells,
+                                                    uint8_t* out) {
+  __shared__ int marked[32];
+  const int k = threadIdx.x & 31, dz = threadIdx.x >> 5;
+  const int64_t cy = (ny + 7) / 8, cx = (nx + 7) / 8;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 32 + k;
+  if (threadIdx.x < 32) marked[k] = 0;
+  __syncthreads();
+  if (i < cells) {
+    const int64_t x0 = i % cx * 8, y0 = i / cx % cy * 8, z = i / (cx * cy) * 8 + dz;
+    uint64_t any = 0;
+    if (z < nz) {
+      uint64_t v[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const uint8_t* row = mask + (z * ny + (y0 + r < ny ? y0 + r : ny - 1)) * nx + x0;  // past the end: the last again
+        if (x0 + 8 <= nx) {
+          __builtin_memcpy(&v[r], row, 8);  // any alignment
+        } else {
+          v[r] = 0;
+          for (int64_t x = x0; x < nx; ++x) v[r] |= row[x - x0];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) any |= v[r];
+    }
+    if (any != 0) marked[k] = 1;  // every writer writes the same
+  }
+  __syncthreads();
+  if (threadIdx.x < 32 && i < cells) out[i] = static_cast<uint8_t>(marked[k]);
+}
+
+// Which cells of 8 x 8 x 64 voxels each pass has to compute (see MaskCells): the
+// base cells within ceil(R / 8) cells along x, then y, then z.  Eight lanes share a
+// cell, each taking every eighth of the rows around it.
+__global__ __launch_bounds__(256) void k_needed_cells(MaskCells c, int64_t cz, int64_t cy, int64_t cx, int64_t xs) {
+  const int part = threadIdx.x & 7;
+  const int64_t j = static_cast<int64_t>(blockIdx.x) * 32 + (threadIdx.x >> 3);
+  const int64_t i = j < cz * cy * xs ? j : cz * cy * xs - 1;
+  const int64_t s = i % xs, y = i / xs % cy, z = i / (xs * cy);
+  const int k = (c.reach + 7) / 8, side = 2 * k + 1;
+  const int64_t xa = 8 * s - k > 0 ? 8 * s - k : 0, xb = 8 * s + 8 + k < cx ? 8 * s + 8 + k : cx;
+  uint32_t need = 0;  // bit 0: y integration, 1: z integration, 2: products
+  for (int r = part; r < side * side; r += 8) {
+    const int dz = r / side - k, dy = r % side - k;
+    if (z + dz < 0 || z + dz >= cz || y + dy < 0 || y + dy >= cy) continue;
+    const uint8_t* row = c.base + ((z + dz) * cy + y + dy) * cx;
+    uint32_t any = 0;
+#pragma unroll 4
+    for (int64_t x = xa; x < xb; ++x) any |= row[x];
+    if (any != 0) need |= 4u | (dz == 0 ? 2u : 0u) | (dz == 0 && dy == 0 ? 1u : 0u);
+  }
+#pragma unroll
+  for (int m = 1; m < 8; m *= 2) need |= __shfl_xor(need, m);
+  if (part != 0 || j != i) return;
+  c.y[i] = need & 1u;
+  c.z[i] = need >> 1 & 1u;
+  c.grad[i] = need >> 2;
+}
+
+hipError_t launch_mask_cells(const GradFusedParams& p, hipStream_t stream) {
+  const MaskCells& c = p.mask;
+  const int64_t cz = cells_of(p.nz), cy = cells_of(p.ny), cx = cells_of(p.nx), xs = p.x_tiles;
+  const int64_t cells = cz * cy * cx;
+  hipLaunchKernelGGL(k_mask_cells, dim3(static_cast<unsigned>((cells + 31) / 32)), dim3(256), 0, stream, c.mask, p.nz,
+                     p.ny, p.nx, cells, c.base);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_needed_cells, dim3(static_cast<unsigned>((cz * cy * xs + 31) / 32)), dim3(256), 0, stream, c, cz,
+                     cy, cx, xs);
+  return hipGetLastError();
 }
 
 // One launch over a table of volumes.  Each entry's block range starts on a
@@ -215,6 +323,23 @@ void k_grad_fused_grouped(const GradFusedGroup p) {
 template <typename Tin, int R>
 hipError_t launch_r(const GradFusedParams& p, hipStream_t stream) {
   const int64_t blocks = p.x_tiles * p.y_tiles * p.nchunks;
+  if (p.cells != nullptr) {
+    const hipError_t e = launch_mask_cells(p, stream);
+    if (e != hipSuccess) return e;
+    if (p.rows == grad_tile_rows(R)) {
+      hipLaunchKernelGGL((k_grad_masked<R, Tin>), dim3(static_cast<unsigned>(blocks)), dim3(kGradTX, grad_tile_rows(R)),
+                         0, stream, p);
+      return hipGetLastError();
+    }
+    if constexpr (grad_rows_supported(R, 4) && grad_tile_rows(R) != 4) {
+      if (p.rows == 4) {
+        hipLaunchKernelGGL((k_grad_masked<R, Tin, 4>), dim3(static_cast<unsigned>(blocks)), dim3(kGradTX, 4), 0, stream,
+                           p);
+        return hipGetLastError();
+      }
+    }
+    return hipErrorInvalidValue;
+  }
   if (p.rows == grad_tile_rows(R)) {
     hipLaunchKernelGGL((k_grad_fused<R, Tin>), dim3(static_cast<unsigned>(blocks)), dim3(kGradTX, grad_tile_rows(R)),
                        0, stream, p);

@@ -300,6 +300,10 @@ int check_path_buffers(const PathArgs& a) {
   return ST_OK;
 }
 
+// Voxels from which a mask's cells are made (two small launches and a read of the
+// mask): below, they cost about what a heart's wall lets the passes leave out.
+static constexpr int64_t kMaskCellsMin = int64_t(1) << 22;
+
 // z pieces of the gradient pass: as many as make the launch shortest, when a piece
 // of c planes costs c + 2R (its halo planes are filtered too) and `tiles` blocks a
 // piece run on `cus` compute units.  A unit holds `fit` blocks at full rate; with k
@@ -415,12 +419,42 @@ void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* 
     p.vec_ok = 1;  // workspace rows: 16-byte aligned
     p.wg = gs; p.wd = ds;
   }
+  // A masked volume: cells that say where each pass is needed.  They live at the
+  // start of the first requested output: every output is undefined until the final
+  // pass, the only one that writes or reads none of them.
+  st::MaskCells mc{};
+  if (plan->fused_grad && a.mask != nullptr && a.n >= kMaskCellsMin) {
+    uint8_t* buf = nullptr;
+    for (void* q : {static_cast<void*>(a.e3), static_cast<void*>(a.evals), static_cast<void*>(a.fa),
+                    static_cast<void*>(a.ha), static_cast<void*>(a.ia), static_cast<void*>(a.flags)})
+      if (buf == nullptr) buf = static_cast<uint8_t*>(q);
+    const int64_t cz = st::cells_of(nz), cy = st::cells_of(ny), xs = (nx + 63) / 64;
+    if (st::mask_cell_bytes(nz, ny, nx) <= a.n) {  // the smallest output holds a byte per voxel
+      mc.mask = a.mask;
+      mc.base = buf;
+      mc.y = buf + cz * cy * st::cells_of(nx);
+      mc.z = mc.y + cz * cy * xs;
+      mc.grad = mc.z + cz * cy * xs;
+      mc.reach = pr;
+      plan->grad.mask = mc;
+      plan->grad.cells = mc.grad;
+    }
+  }
   // integration: z pass, y pass (6 components each)
   st::StridedJob j[6];
   for (int c = 0; c < 6; ++c) j[c] = st::StridedJob{B[c], A[c], nullptr};
   strided(plan->int_z, true, false, 6, j, pr, gr, nullptr);
   for (int c = 0; c < 6; ++c) j[c] = st::StridedJob{A[c], B[c], nullptr};
   strided(plan->int_y, false, false, 6, j, pr, gr, nullptr);
+  if (mc.mask != nullptr) {
+    const int64_t xs = (nx + 63) / 64, row = xs, plane = st::cells_of(ny) * xs;
+    plan->int_z.cells = mc.z;
+    plan->int_z.cell_axis = plane;
+    plan->int_z.cell_other = row;
+    plan->int_y.cells = mc.y;
+    plan->int_y.cell_axis = row;
+    plan->int_y.cell_other = plane;
+  }
   // x integration fused with eigen, FA, angles
   st::XFinalParams& p = plan->fin;
   std::memset(&p, 0, sizeof(p));

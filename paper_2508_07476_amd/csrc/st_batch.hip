@@ -805,7 +805,7 @@ int st_batch_plan(const st_batch* b, int* grouped, int* rounds, int* kernels) {
       for (const st::host::PathArgs& a : b->chunks) {
         st::host::PathPlan pl;
         st::host::plan_path(a, b->ws, st::host::LaunchShape{}, &pl);
-        k += pl.fused_grad ? 4 : 7;
+        k += (pl.fused_grad ? 4 : 7) + (pl.fused_grad && pl.grad.cells != nullptr ? 2 : 0);
       }
     }
     *kernels = static_cast<int>(k);

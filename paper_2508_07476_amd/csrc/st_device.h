@@ -21,6 +21,43 @@ __device__ __forceinline__ int reflect_lane(int m, int n) {
   return m < n ? m : p - 1 - m;
 }
 
+// Runs of marked cells along an axis, for one wave: positions [a, a + len) of it,
+// cell c (positions 8 c .. 8 c + 7) marked by cells[c * stride].  Up to 64 cells are
+// looked at together, one by each lane; gaps of up to two cells are closed, since
+// starting a run costs as much.  next() gives the runs in order, cut to [a, a + len).
+struct CellRuns {
+  const uint8_t* cells;
+  int64_t stride;
+  int a, end;        // positions
+  int c;             // first cell of `bits`
+  uint64_t bits;     // marked cells not given yet
+  __device__ __forceinline__ void look() {
+    const int k = c + static_cast<int>(__lane_id());
+    const uint64_t b = __ballot(8 * k < end && cells[(8 * k < end ? k : c) * stride] != 0);
+    bits = b | (((b << 1) | (b << 2)) & ((b >> 1) | (b >> 2)));
+  }
+  __device__ __forceinline__ CellRuns(const uint8_t* cells_, int64_t stride_, int a_, int len)
+      : cells(cells_), stride(stride_), a(a_), end(a_ + len), c(a_ / 8) {
+    look();
+  }
+  __device__ __forceinline__ bool next(int& ra, int& rlen) {
+    while (bits == 0) {
+      c += 64;
+      if (8 * c >= end) return false;
+      look();
+    }
+    const int lo = __builtin_ctzll(bits);
+    const uint64_t rest = ~(bits >> lo);  // first unmarked cell after lo (rest is 0 only for 64 marked cells)
+    const int n = rest == 0 ? 64 : __builtin_ctzll(rest);
+    const int hi = lo + n < 64 ? lo + n : 64;
+    bits = hi == 64 ? 0 : bits >> hi << hi;
+    ra = 8 * (c + lo) > a ? 8 * (c + lo) : a;
+    const int re = 8 * (c + hi) < end ? 8 * (c + hi) : end;
+    rlen = re - ra;
+    return true;
+  }
+};
+
 // Entry of a grouped launch that block b belongs to: the last e with
 // first[e] <= b (b is wave-uniform, so the search runs on the scalar unit).
 __device__ __forceinline__ int group_entry(const int64_t* __restrict__ first, int count, int64_t b) {

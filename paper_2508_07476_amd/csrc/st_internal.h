@@ -65,6 +65,11 @@ struct StridedGeo {
   int64_t nx;
   int64_t x_tiles;   // ceil(nx / 64)
   int64_t o_tiles;   // ceil(n_other / 4)
+  // Masked launches (else NULL): which cells of 8 x 8 x 64 voxels the later passes
+  // read, one byte each; cell strides along the filtered and the other axis.
+  // Grouped launches do without.
+  const uint8_t* cells;
+  int64_t cell_axis, cell_other;
 };
 
 struct StridedParams : StridedGeo {
@@ -144,9 +149,30 @@ struct GradGeo {
   int64_t chunk;      // z outputs per block
   int nchunks;
   int rows;           // output rows (y) per block, one wave each: grad_rows_supported(R, rows)
+  const uint8_t* cells;  // masked launches: the cells ([z][y][x] of 8 x 8 x 64 voxels) to compute, else NULL
 };
 
+// Which parts of the workspace a masked volume needs.  The mask gates the outputs
+// only, so a pass is needed where a later one reads it: the y integration within
+// R (the integration's compiled radius) of the mask along x, the z integration
+// within R of that along y, the products within R of that along z.  One byte per
+// cell of 8 x 8 x 64 (z, y, x) voxels each, made from the mask by two kernels that
+// launch_grad_fused runs first.
+struct MaskCells {
+  const uint8_t* mask;  // NULL: no cells
+  uint8_t* base;        // the mask itself by cells of 8^3, then the three below
+  uint8_t* y;
+  uint8_t* z;
+  uint8_t* grad;
+  int reach;            // R
+};
+inline int64_t cells_of(int64_t n) { return (n + 7) / 8; }
+inline int64_t mask_cell_bytes(int64_t nz, int64_t ny, int64_t nx) {
+  return cells_of(nz) * cells_of(ny) * (cells_of(nx) + 3 * ((nx + 63) / 64));
+}
+
 struct GradFusedParams : GradGeo {
+  MaskCells mask;
   Taps wg;
   Taps wd;
 };
