@@ -261,7 +261,7 @@ __device__ __forceinline__ void xfinal_block(const XFinalGeo& p, const Taps& w, 
       pz = static_cast<double>(pzi);
       py = static_cast<double>(pyi);
     }
-#pragma unroll 1
+#pragma unroll 2  // renames half of the rotation below; 4 needs 136 VGPRs, a wave less per SIMD
     for (int v = 0; v < kXVec; ++v) {
       const int xv = x + v;
       const bool inside = (inside_bits >> v) & 1u;
@@ -273,27 +273,24 @@ __device__ __forceinline__ void xfinal_block(const XFinalGeo& p, const Taps& w, 
         acc[c][1] = acc[c][2];
         acc[c][2] = acc[c][3];
       }
-      float res[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      float l1 = 0.f, l2 = 0.f, l3 = 0.f;
-      uint32_t fl = ST_FLAG_OUTSIDE_MASK;
-      if (inside) {
-        EigOut o;
-        eig_smallest(s6, o);
-        res[0] = static_cast<float>(o.vz);
-        res[1] = static_cast<float>(o.vy);
-        res[2] = static_cast<float>(o.vx);
-        res[3] = o.fa;
-        l1 = o.l1; l2 = o.l2; l3 = o.l3;
-        fl = o.degenerate ? ST_FLAG_DEGENERATE : 0u;
-        if (p.has_axis && fibre_angles(o.vz, o.vy, o.vx, p.center, p.dir, pz, py,
-                                       static_cast<double>(xv), res[4], res[5]))
-          fl |= ST_FLAG_ON_AXIS;
-      }
+      // every lane solves its voxel; those outside the mask select zeros
+      EigOut o;
+      eig_smallest(s6, p.evals != nullptr, o);
+      float res[6] = {o.vz, o.vy, o.vx, o.fa, 0.f, 0.f};
+      uint32_t fl = o.degenerate ? ST_FLAG_DEGENERATE : 0u;
+      if (p.has_axis && fibre_angles(o.vz, o.vy, o.vx, p.center, p.dir, pz, py,
+                                     static_cast<double>(xv), res[4], res[5]))
+        fl |= ST_FLAG_ON_AXIS;
+      fl = inside ? fl : ST_FLAG_OUTSIDE_MASK;
 #pragma unroll
-      for (int q = 0; q < 6; ++q) seg[q][kXVec * l + v] = res[q];
-      if (row_ok && xv < nxi && p.evals) {  // optional output: scalar stores
-        const int64_t i = base + xv;
-        p.evals[i] = l1; p.evals[n + i] = l2; p.evals[2 * n + i] = l3;
+      for (int q = 0; q < 6; ++q) seg[q][kXVec * l + v] = inside ? res[q] : 0.f;
+      if (p.evals) {  // optional output: scalar stores
+        if (row_ok && xv < nxi) {
+          const int64_t i = base + xv;
+          p.evals[i] = inside ? o.l1 : 0.f;
+          p.evals[n + i] = inside ? o.l2 : 0.f;
+          p.evals[2 * n + i] = inside ? o.l3 : 0.f;
+        }
       }
       flag_word |= (fl & 0xffu) << (8 * v);
     }
