@@ -7,25 +7,33 @@
 //   g_z = Dz (Gx Gy V),  g_y = Gz (Gx Dy V),  g_x = Gz (Dx Gy V).
 // A block of TY waves owns a TY (y) x 64 (x) tile of output columns and a chunk
 // of z outputs (by default TY = 8 up to radius 6, where 8-row blocks still fit
-// four waves per SIMD without spilling, else 4; a 4-row variant is also built
-// up to radius 6 for the batch autotuner).  For every input plane (z halo of R on
-// each side, reflected at the faces) the (TY + 2R) x (64 + 2R) input tile is
-// staged in LDS, in two buffers used by alternate planes.  A plane's loads stay
-// raw in registers (converted only when staged: a conversion beside the load
-// waits for it) and have a whole plane's work to arrive: they are issued between
-// the x and the z filter of the plane two before and staged at the same point of
-// the next.  What bounds the pass is VALU issue (62 % of the cycles) and
-// LDS reads at a clock held down by power; with the loads waited for where they
-// were issued it took 1389 us at radius 6 on 512^3 u16, against 1245 (7258 against
-// 6138 at radius 8 on 512 x 1024 x 1024).  Each wave filters
-// along y the 64 + 2R columns of its own tile row, which only it reads in the
-// x filter, so one block barrier per plane (after the staging) suffices: a
-// wave that writes plane j + 1's buffer has passed plane j's barrier, and one
-// that would overwrite plane j's buffer (at j + 2) waits at plane j + 1's for
-// every wave to finish reading it.  Each
-// column's z window lives in registers; the plane loop is expanded to the window
-// length (a fold over an index sequence), so every plane's results land in a
-// register fixed at compile time and the window never moves.
+// four waves per SIMD, else 4; a 4-row variant is also built up to radius 6 for
+// the batch autotuner).  The input planes (z halo of R on each side, reflected at
+// the faces) are taken in pairs.  For every pair the (TY + 2R) x (64 + 2R) input
+// tiles are staged in LDS, in two buffers used by alternate pairs.  A pair's loads
+// stay raw in registers (converted only when staged: a conversion beside the load
+// waits for it) and have a whole pair's work to arrive: they are issued between
+// the x and the z filter of the pair two before and staged at the same point of
+// the next.  Each wave filters along y the 64 + 2R columns of its own tile row,
+// which only it reads in the x filter, so one block barrier per pair (after the
+// staging) suffices: a wave that writes pair j + 1's buffer has passed pair j's
+// barrier, and one that would overwrite pair j's buffer (at j + 2) waits at pair
+// j + 1's for every wave to finish reading it.
+//
+// What bounds the pass is VALU issue and LDS reads, each busy for about two thirds
+// of it, at a clock held down by power.  The pairs save both: the y filter takes
+// three wave steps for two planes instead of four (the 2R columns past the 64 of
+// both planes fill one step together), and the x filter gives each half wave one
+// plane, two neighbouring columns to a lane, so that a value read serves both (40 %
+// fewer LDS bytes a voxel at R = 8; the sums return to their columns through LDS).
+// Six-row tiles at radius 8 would stage less but leave room for one block a
+// compute unit (8.6 ms below).  Times of the pass, u16: 512 x 1024 x 1024 at radius
+// 8: 7.26 ms with the loads waited for where they were issued, 5.98 plane by plane,
+// 5.32 by pairs; a masked 512^3 at radius 6: 1.28 ms plane by plane, 1.10 by pairs.
+//
+// Each column's z window lives in registers; the loop is expanded over the window's
+// slots (a fold over an index sequence), so every plane's results land in a register
+// fixed at compile time and the window never moves.
 // Products leave with non-temporal stores into workspace planes whose rows have
 // the workspace pitch (the input volume has rows of nx).
 #include <utility>
@@ -46,8 +54,13 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
   // The smoothing taps are symmetric about the centre (bit for bit, as built):
   // only taps 0..R are read, so R + 1 of them occupy scalar registers.
   auto tg = [&](int k) { return wg.w[k <= R ? k : 2 * R - k]; };
-  __shared__ float raw[2][RY * RX];   // input planes (exact in float32), alternating
-  __shared__ double yb[2][TY * RX];   // y-filtered plane, float64
+  constexpr int NP = 2;          // input planes per step (see above)
+  constexpr int S = W + NP - 1;  // slots of a z window
+  // doubles a wave keeps to itself: G and D of its row in each plane, filtered along
+  // y, then (the x filter has read them) the three results of its 64 columns
+  constexpr int NY = 2 * RX > 3 * TX ? 2 * NP * RX : 3 * NP * TX;
+  __shared__ float raw[2][NP][RY * RX];  // input planes of a step (exact in float32), alternating
+  __shared__ __attribute__((aligned(16))) double own[TY][NY];
 
   const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * 64 + tx;
   // Blocks are dealt round-robin to the 8 XCDs (each with its own L2); give each
@@ -88,116 +101,147 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
     off[j] = gy * static_cast<int>(nx) + gx;
   }
   auto run = [&](int z0, int len) {  // output planes z0 .. z0 + len - 1
-    // the input plane in flight, as loaded: a conversion here would wait for it
-    Tin pf[NSTAGE];
-    auto fetch = [&](int zi) {  // loads of input plane zi into pf
-      const Tin* src = vol + static_cast<int64_t>(reflect_lane(zi, nzi)) * plane;
+    const int nplanes = len + 2 * R;  // at least 3
+    const int nsteps = (nplanes + NP - 1) / NP;  // a last step may repeat its plane
+    // the input planes in flight, as loaded: a conversion here would wait for them
+    Tin pf[NP][NSTAGE];
+    auto fetch = [&](int j) {  // loads of step j's planes into pf
 #pragma unroll
-      for (int j = 0; j < NSTAGE; ++j) pf[j] = src[off[j]];  // halo re-read by neighbours: keep cached
-    };
-
-    auto stage = [&](int j) {  // the fetched plane into step j's buffer
-      float* rb = raw[j & 1];
+      for (int e = 0; e < NP; ++e) {
+        const int i = NP * j + e;
+        const int zi = z0 - R + (e == 0 || i < nplanes ? i : nplanes - 1);
+        const Tin* src = vol + static_cast<int64_t>(reflect_lane(zi, nzi)) * plane;
 #pragma unroll
-      for (int t = 0; t < NSTAGE; ++t) {
-        const int s = tid + NT * t;
-        if (s < RX * RY) rb[s] = static_cast<float>(pf[t]);
+        for (int t = 0; t < NSTAGE; ++t) pf[e][t] = src[off[t]];  // halo re-read by neighbours: keep cached
       }
     };
 
-    // Filter plane step j (staged) along y then x: the three partial results of
-    // this thread's column.  Then stage plane step j + 1, whose loads have been in
-    // flight since the step before, and issue those of step j + 2: the wait for
-    // loads also waits for the products stored before them, which by then had the
-    // two filters' time to leave.
-    auto filter_plane = [&](int j, int nplanes, double& a, double& bq, double& c) {
-      const float* rb = raw[j & 1];
-      __syncthreads();
-      // y filter of the wave's own row (columns tx and tx + 64 of RX): only this
-      // wave reads it, so no block barrier separates it from the x filter
+    auto stage = [&](int j) {  // the fetched planes into step j's buffer
 #pragma unroll
-      for (int q = 0; q < (RX + 63) / 64; ++q) {
-        const int col = tx + 64 * q;
-        if (col < RX) {
-          double g = 0.0, d = 0.0;
+      for (int e = 0; e < NP; ++e) {
+        float* rb = raw[j & 1][e];
 #pragma unroll
-          for (int k = 0; k < W; ++k) {
-            const double v = rb[(ty + k) * RX + col];
-            g = fma(tg(k), v, g);
-            d = fma(wd.w[k], v, d);
-          }
-          yb[0][ty * RX + col] = g;
-          yb[1][ty * RX + col] = d;
+        for (int t = 0; t < NSTAGE; ++t) {
+          const int s = tid + NT * t;
+          if (NT * (t + 1) <= RX * RY || s < RX * RY) rb[s] = static_cast<float>(pf[e][t]);
         }
       }
+    };
+
+    auto wave_fence = [] {  // orders the wave's own LDS accesses
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      double ga = 0.0, gb = 0.0, dc = 0.0;
+    };
+    double* const mine = own[ty];
+
+    // Filter the planes of step j (staged) along y then x, which leaves the three
+    // partial results of the wave's columns in each in `mine`.  Then stage step
+    // j + 1, whose loads have been in flight since the step before, and issue those of
+    // step j + 2: the wait for loads also waits for the products stored before them,
+    // which by then had the two filters' time to leave.
+    auto filter_step = [&](int j) {
+      __syncthreads();
+      // y filter of the wave's own row; only this wave reads it, so no block barrier
+      // separates it from the x filter.  First 64 columns of each plane, then the 2 R
+      // left of all planes together.
 #pragma unroll
-      for (int k = 0; k < W; ++k) {
-        const double u = yb[0][ty * RX + tx + k];
-        const double w = yb[1][ty * RX + tx + k];
-        ga = fma(tg(k), u, ga);
-        dc = fma(wd.w[k], u, dc);
-        gb = fma(tg(k), w, gb);
+      for (int q = 0; q <= NP; ++q) {
+        const int e = q < NP ? q : tx / (2 * R);
+        const int col = q < NP ? tx : 64 + tx - 2 * R * e;
+        if (q < NP || tx < 2 * R * NP) {
+          const float* rb = raw[j & 1][e] + ty * RX + col;
+          double g = 0.0, d = 0.0;
+#pragma unroll
+          for (int k = 0; k < W; ++k) {
+            const double v = rb[k * RX];
+            g = fma(tg(k), v, g);
+            d = fma(wd.w[k], v, d);
+          }
+          mine[2 * e * RX + col] = g;
+          mine[(2 * e + 1) * RX + col] = d;
+        }
       }
-      // materialise the three results here: otherwise the compiler sinks these
-      // sums towards their use in the z filter and keeps every LDS value alive
-      asm volatile("" : "+v"(ga), "+v"(gb), "+v"(dc));
-      if (j + 1 < nplanes) {
+      wave_fence();
+      // x filter: 64 / NP lanes for each plane, NP neighbouring columns a lane (each
+      // value read once for all of them)
+      double ga[NP], gb[NP], dc[NP];
+#pragma unroll
+      for (int v = 0; v < NP; ++v) ga[v] = gb[v] = dc[v] = 0.0;
+      const int e = tx / (64 / NP), c0 = NP * (tx % (64 / NP));
+      const double* const us = mine + 2 * e * RX + c0;
+#pragma unroll
+      for (int i = 0; i < W + NP - 1; ++i) {
+        const double u = us[i], w = us[RX + i];
+#pragma unroll
+        for (int v = 0; v < NP; ++v) {
+          const int k = i - v;
+          if (k < 0 || k >= W) continue;
+          ga[v] = fma(tg(k), u, ga[v]);
+          dc[v] = fma(wd.w[k], u, dc[v]);
+          gb[v] = fma(tg(k), w, gb[v]);
+        }
+      }
+      wave_fence();  // the sums are formed: their inputs' place is free
+#pragma unroll
+      for (int v = 0; v < NP; ++v) {
+        double* const res = mine + TX * e + c0 + v;
+        res[0] = ga[v];            // Gx Gy V -> Dz gives g_z
+        res[NP * TX] = gb[v];      // Gx Dy V -> Gz gives g_y
+        res[2 * NP * TX] = dc[v];  // Dx Gy V -> Gz gives g_x
+      }
+      wave_fence();
+      if (j + 1 < nsteps) {
         stage(j + 1);
-        if (j + 2 < nplanes) fetch(z0 - R + j + 2);
+        if (j + 2 < nsteps) fetch(j + 2);
       }
-      a = ga;   // Gx Gy V   -> Dz gives g_z
-      bq = gb;  // Gx Dy V   -> Gz gives g_y
-      c = dc;   // Dx Gy V   -> Gz gives g_x
     };
 
     const bool active = (x0 + tx < nx) && (y0 + ty < ny);
     const int64_t out_col = (y0 + ty) * p.opitch + (x0 + tx);
     const int64_t out_plane = ny * p.opitch;
 
-    // z windows: slot (j + k) mod W of w* holds the column's partial results of
-    // input plane j - 2R + k at plane step j; the plane loop is expanded W times
-    // so that every slot index is static (no register moves)
-    double wa[W], wb[W], wc[W];
-    const int nplanes = len + 2 * R;  // at least 3
-    fetch(z0 - R);
+    // z windows: slot j mod S holds the column's partial results of input plane j (W
+    // of them are live).  The plane loop is expanded S times so that every slot index
+    // is static (no register moves)
+    double wa[S], wb[S], wc[S];
+    fetch(0);
     stage(0);
-    fetch(z0 - R + 1);
+    fetch(1);
 #pragma unroll 1
-    for (int jb = 0; jb < nplanes; jb += W) {  // block-uniform trip count
-      auto step = [&]<int J>(std::integral_constant<int, J>) {
-        const int j = jb + J;
-        if (j < nplanes) {
-          double a, bq, c;
-          filter_plane(j, nplanes, a, bq, c);
-          constexpr int S = (J + 2 * R) % W;
-          wa[S] = a;
-          wb[S] = bq;
-          wc[S] = c;
-          if (j >= 2 * R && active) {
-            double gz = 0.0, gy = 0.0, gx = 0.0;
+    for (int jb = 0; jb < nplanes; jb += S) {  // block-uniform trip count
+      auto step = [&]<int J>(std::integral_constant<int, J>) {  // planes jb + J .. jb + J + NP - 1
+        if (jb + J < nplanes) {
+          filter_step((jb + J) / NP);
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
-              gz = fma(wd.w[k], wa[(J + k) % W], gz);
-              gy = fma(tg(k), wb[(J + k) % W], gy);
-              gx = fma(tg(k), wc[(J + k) % W], gx);
+          for (int e = 0; e < NP; ++e) {
+            const int j = jb + J + e;
+            wa[J + e] = mine[TX * e + tx];
+            wb[J + e] = mine[TX * (NP + e) + tx];
+            wc[J + e] = mine[TX * (2 * NP + e) + tx];
+            if (j >= 2 * R && j < nplanes && active) {
+              double gz = 0.0, gy = 0.0, gx = 0.0;
+#pragma unroll
+              for (int k = 0; k < W; ++k) {
+                gz = fma(wd.w[k], wa[(J + e + k + NP) % S], gz);
+                gy = fma(tg(k), wb[(J + e + k + NP) % S], gy);
+                gx = fma(tg(k), wc[(J + e + k + NP) % S], gx);
+              }
+              const int64_t i = static_cast<int64_t>(z0 + j - 2 * R) * out_plane + out_col;
+              __builtin_nontemporal_store(static_cast<float>(gz * gz), p.prod[0] + i);
+              __builtin_nontemporal_store(static_cast<float>(gz * gy), p.prod[1] + i);
+              __builtin_nontemporal_store(static_cast<float>(gz * gx), p.prod[2] + i);
+              __builtin_nontemporal_store(static_cast<float>(gy * gy), p.prod[3] + i);
+              __builtin_nontemporal_store(static_cast<float>(gy * gx), p.prod[4] + i);
+              __builtin_nontemporal_store(static_cast<float>(gx * gx), p.prod[5] + i);
             }
-            const int64_t i = static_cast<int64_t>(z0 + j - 2 * R) * out_plane + out_col;
-            __builtin_nontemporal_store(static_cast<float>(gz * gz), p.prod[0] + i);
-            __builtin_nontemporal_store(static_cast<float>(gz * gy), p.prod[1] + i);
-            __builtin_nontemporal_store(static_cast<float>(gz * gx), p.prod[2] + i);
-            __builtin_nontemporal_store(static_cast<float>(gy * gy), p.prod[3] + i);
-            __builtin_nontemporal_store(static_cast<float>(gy * gx), p.prod[4] + i);
-            __builtin_nontemporal_store(static_cast<float>(gx * gx), p.prod[5] + i);
           }
+          wave_fence();  // the results are read: the next y filter overwrites them
         }
       };
-      [&]<int... J>(std::integer_sequence<int, J...>) {
-        (step(std::integral_constant<int, J>{}), ...);
-      }(std::make_integer_sequence<int, W>{});
+      [&]<int... B>(std::integer_sequence<int, B...>) {
+        (step(std::integral_constant<int, NP * B>{}), ...);
+      }(std::make_integer_sequence<int, S / NP>{});
     }
   };
   if constexpr (MASKED) {
@@ -215,18 +259,18 @@ __device__ __forceinline__ void grad_fused_block(const GradGeo& p, const Taps& w
 }
 
 template <int R, typename Tin, int TY = grad_tile_rows(R)>
-__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 ? 4 : 1)))
+__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 || R <= 5 ? 4 : 3)))
 void k_grad_fused(const GradFusedParams p) {
   grad_fused_block<R, Tin, TY>(p, p.wg, p.wd, blockIdx.x);
 }
 
 // With a wall mask that fills 0.49 of 512^3 u16 (sigma 1.5, rho 4) the gradient pass
-// takes 1.18 ms instead of 1.25 (every tile is resident at once, so the fullest
-// column of blocks still ends it) and 0.04 for the cells, the integrations 1.10 and
+// took 1.18 ms instead of 1.25 (plane by plane; every tile is resident at once, so the
+// fullest column of blocks still ends it) and 0.04 for the cells, the integrations 1.10 and
 // 1.02 instead of 1.38 and 1.35; 400 x 640 x 600 (sigma 2, rho 6): 1.56 instead of
 // 2.01, 1.37 and 1.21 instead of 1.88 and 1.84.
 template <int R, typename Tin, int TY = grad_tile_rows(R)>
-__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 ? 4 : 1)))
+__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 || R <= 5 ? 4 : 3)))
 void k_grad_masked(const GradFusedParams p) {
   grad_fused_block<R, Tin, TY, true>(p, p.wg, p.wd, blockIdx.x);
 }
@@ -310,7 +354,7 @@ hipError_t launch_mask_cells(const GradFusedParams& p, hipStream_t stream) {
 // multiple of 8, so the XCD-aware remap inside a volume sees its own blocks
 // dealt round-robin to the 8 XCDs as in a launch of its own.
 template <int R, typename Tin, int TY>
-__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 ? 4 : 1)))
+__global__ __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(TY == 8 || R <= 5 ? 4 : 3)))
 void k_grad_fused_grouped(const GradFusedGroup p) {
   const int64_t b = blockIdx.x;
   const int e = group_entry(p.g.first, p.g.count, b);
