@@ -310,8 +310,9 @@ static constexpr int64_t kMaskCellsMin = int64_t(1) << 22;
 // of them it takes max(k / fit, 0.3 + 0.7 k / fit) of a full unit's time a plane
 // (measured on 64^3 to 300^3 volumes at radii 4, 6 and 8).  Alone on the chip the
 // fullest unit ends the launch, so k is rounded up; beside other launches the rest
-// of it is theirs.  A 64^3 volume at radius 4 takes 16 us in 32 pieces, 46 in the
-// two that pieces of 8R planes allowed; 512^3 stays whole.
+// of it is theirs.  A 64^3 volume at radius 4 took 16 us in 32 pieces, 46 in the
+// two that pieces of 8R planes allowed (13.8 in 32 since planes are filtered in
+// pairs); 512^3 stays whole.
 static int64_t grad_pieces(int64_t tiles, int64_t nz, int R, int64_t cus, int64_t fit, bool alone) {
   int64_t best = 1;
   double cost = 0.0;
@@ -401,7 +402,7 @@ void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* 
     p.y_tiles = (ny + rows - 1) / rows;
     // grad_min_blocks counts blocks of four waves, four to a compute unit
     const int64_t cus = std::max<int64_t>(1, shape.grad_min_blocks / 4);
-    const int64_t nch = grad_pieces(p.x_tiles * p.y_tiles, nz, ps, cus, rows == 8 ? 2 : ps <= 6 ? 4 : 3,
+    const int64_t nch = grad_pieces(p.x_tiles * p.y_tiles, nz, ps, cus, rows == 8 ? 2 : ps <= 5 ? 4 : 3,
                                     cus >= 256);
     p.chunk = (nz + nch - 1) / nch;
     p.nchunks = static_cast<int>((nz + p.chunk - 1) / p.chunk);
