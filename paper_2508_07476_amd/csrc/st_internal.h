@@ -178,7 +178,7 @@ struct GradFusedParams : GradGeo {
 };
 constexpr int kGradTX = 64;
 // Output rows per block (one wave per row) by default: 8 where the kernel fits
-// four waves per SIMD without spilling, else 4.
+// four waves per SIMD (24 bytes of spill in the masked form at radius 6), else 4.
 constexpr int grad_tile_rows(int R) { return R <= 6 ? 8 : 4; }
 // Tile rows compiled for radius R: the default, and 4 rows up to radius 6 too.
 constexpr bool grad_rows_supported(int R, int rows) {
