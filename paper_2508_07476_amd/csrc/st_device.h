@@ -153,26 +153,23 @@ __device__ __forceinline__ bool fibre_angles(float uz, float uy, float ux, const
 
 // Null vector of A - mu I (A symmetric, components zz, zy, zx, yy, yx, xx):
 // the largest of the three cross products of pairs of its rows (Kopp 2008).
-// Returns it unnormalised with its squared length.  The cross products are the
-// columns of the adjugate of A - mu I, which is symmetric, so six entries give
-// all three; it is also k v v^T for the null vector v, so the longest column is
-// the one of the largest diagonal entry and only its length is formed.
+// Returns it unnormalised with its squared length.  The nine entries are those of
+// a symmetric matrix, but are formed each on its own: where mu is a double
+// eigenvalue all three products are rounding errors or lengths that tie, and which
+// of them is taken (the first that none exceeds) decides the e3 that comes out.
 __device__ __forceinline__ void null_vector(double zz, double zy, double zx, double yy, double yx,
                                             double xx, double mu, double& vz, double& vy,
                                             double& vx, double& nn) {
   const double a = zz - mu, b = yy - mu, c = xx - mu;
-  const double c00 = b * c - yx * yx, c11 = a * c - zx * zx, c22 = a * b - zy * zy;
-  const double c01 = yx * zx - zy * c, c02 = zy * yx - zx * b, c12 = zx * zy - a * yx;
-  const double d0 = fabs(c00), d1 = fabs(c11), d2 = fabs(c22);
-  const bool first = d0 >= d1;
-  vz = first ? c00 : c01;
-  vy = first ? c01 : c11;
-  vx = first ? c02 : c12;
-  const bool last = d2 > (first ? d0 : d1);
-  vz = last ? c02 : vz;
-  vy = last ? c12 : vy;
-  vx = last ? c22 : vx;
-  nn = vz * vz + vy * vy + vx * vx;
+  const double c0z = zy * yx - zx * b, c0y = zx * zy - a * yx, c0x = a * b - zy * zy;  // r0 x r1
+  const double c1z = zy * c - zx * yx, c1y = zx * zx - a * c, c1x = a * yx - zy * zx;  // r0 x r2
+  const double c2z = b * c - yx * yx, c2y = yx * zx - zy * c, c2x = zy * yx - b * zx;  // r1 x r2
+  const double n0 = c0z * c0z + c0y * c0y + c0x * c0x;
+  const double n1 = c1z * c1z + c1y * c1y + c1x * c1x;
+  const double n2 = c2z * c2z + c2y * c2y + c2x * c2x;
+  vz = c0z; vy = c0y; vx = c0x; nn = n0;
+  if (n1 > nn) { vz = c1z; vy = c1y; vx = c1x; nn = n1; }
+  if (n2 > nn) { vz = c2z; vy = c2y; vx = c2x; nn = n2; }
 }
 
 // sin and cos of x in [0, pi/3] by their Taylor series through x^11 / x^12
@@ -223,10 +220,9 @@ struct EigOut {
 // here, so the solution runs straight through and the voxels it does not apply
 // to (no trace, isotropic to working precision, no null vector) take their
 // defaults by selection at the end; l1..l3 are formed only where asked for.
-// With that, the six distinct cross-product entries and the voxel loop's unroll
-// by two the final pass issues 607 vector instructions a voxel instead of 649
-// at R = 24, and takes 10.26 ms instead of 10.64 on 512 x 1024 x 1024 voxels
-// (1.92 both at R = 16 on a masked 512^3, which its loads hold back as well).
+// With that and the voxel loop's unroll by two the final pass takes 10.3 to 10.4 ms
+// instead of 10.64 on 512 x 1024 x 1024 at R = 24 (1.92 both at R = 16 on a masked
+// 512^3, which its loads hold back as well).
 __device__ __forceinline__ void eig_smallest(const double s6[6], bool want_evals, EigOut& o) {
   const double zz = s6[0], zy = s6[1], zx = s6[2], yy = s6[3], yx = s6[4], xx = s6[5];
   const double tr = zz + yy + xx;
