@@ -276,9 +276,9 @@ __device__ __forceinline__ void xfinal_block(const XFinalGeo& p, const Taps& w, 
       // every lane solves its voxel; those outside the mask select zeros
       EigOut o;
       eig_smallest(s6, p.evals != nullptr, o);
-      float res[6] = {o.vz, o.vy, o.vx, o.fa, 0.f, 0.f};
+      float res[6] = {static_cast<float>(o.vz), static_cast<float>(o.vy), static_cast<float>(o.vx), o.fa, 0.f, 0.f};
       uint32_t fl = o.degenerate ? ST_FLAG_DEGENERATE : 0u;
-      if (p.has_axis && fibre_angles(o.vz, o.vy, o.vx, p.center, p.dir, pz, py,
+      if (p.has_axis && fibre_angles(res[0], res[1], res[2], p.center, p.dir, pz, py,
                                      static_cast<double>(xv), res[4], res[5]))
         fl |= ST_FLAG_ON_AXIS;
       fl = inside ? fl : ST_FLAG_OUTSIDE_MASK;

@@ -192,7 +192,7 @@ __device__ __forceinline__ double rsq64(double a) {
 }
 
 struct EigOut {
-  float vz, vy, vx;   // unit e3, canonical sign
+  double vz, vy, vx;  // unit e3, canonical sign
   float l1, l2, l3;   // lambda1 >= lambda2 >= lambda3
   float fa;
   bool degenerate;    // trace <= 0 or (lambda2 - lambda3) / trace < 1e-3
@@ -275,13 +275,11 @@ __device__ __forceinline__ void eig_smallest(const double s6[6], bool want_evals
   // canonical sign: largest |component| positive, ties to the lower axis (z, then y)
   const double az = fabs(vz), ay = fabs(vy), ax = fabs(vx);
   const double lead = (az >= ay && az >= ax) ? vz : (ay >= ax ? vy : vx);
-  // one Newton step leaves 2^-44, far below the float32 rounding of the result
-  double inv = __builtin_amdgcn_rsq(nn);
-  inv = inv * fma(-0.5 * nn * inv, inv, 1.5);
+  double inv = rsq64(nn);
   inv = lead < 0.0 ? -inv : inv;
-  o.vz = found ? static_cast<float>(vz * inv) : 1.f;
-  o.vy = found ? static_cast<float>(vy * inv) : 0.f;
-  o.vx = found ? static_cast<float>(vx * inv) : 0.f;
+  o.vz = found ? vz * inv : 1.0;
+  o.vy = found ? vy * inv : 0.0;
+  o.vx = found ? vx * inv : 0.0;
 }
 
 }  // namespace st

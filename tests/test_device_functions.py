@@ -30,3 +30,7 @@ def _run(name, tmp_path, *extra):
 
 def test_ties_between_equal_cross_products(tmp_path):
     _run("eigen_ties", tmp_path)
+
+
+def test_e3_is_of_unit_length_in_float64(tmp_path):
+    _run("eigen_unit", tmp_path)
