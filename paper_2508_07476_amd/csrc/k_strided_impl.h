@@ -72,7 +72,7 @@ __device__ __forceinline__ void strided_block(const StridedGeo& p, const Taps& w
 
     // win: the 2R+1 samples of the current output; pre: the newest sample of each
     // output of the current block of W outputs, loaded one block ahead so that W
-    // loads per lane are always in flight (past the chunk's last, that one again).
+    // loads per lane are always in flight (of a shorter piece's first block, the last again).
     double win[W];
     float pre[W];
 #pragma unroll
@@ -80,15 +80,19 @@ __device__ __forceinline__ void strided_block(const StridedGeo& p, const Taps& w
 #pragma unroll
     for (int j = 0; j < W; ++j) pre[j] = sample(2 * R + (j < len ? j : len - 1));
 
-    // One output.  A whole block's steps hold no branch around a load or a store:
-    // vector memory is waited for by counting what was issued after it, and across
-    // a branch that may or may not have issued something the count drops to none,
-    // so that every block would end in waiting for all its loads and stores.  A lane
-    // past the row's end carries its last column, and stores the same value there.
+    // One output.  The steps of a block whose outputs and next loads are all the
+    // piece's (WHOLE) hold no branch around a load or a store: vector memory is
+    // waited for by counting what was issued after it, and across a branch that may
+    // or may not have issued something the count drops to none, so that every block
+    // would end in waiting for all its loads and stores.  The piece's last blocks do
+    // have the branches: a load past the piece, even of a sample that is there, costs
+    // what a needed one does (R = 16, y pass: axes of 33 took 107 us on 160 x 33 x
+    // 1024, 75 without them; of 45 108 and 98 us).  A lane past the row's end carries
+    // its last column, and stores the same value there.
     auto step = [&]<int J, bool WHOLE>(std::integral_constant<int, J>, std::bool_constant<WHOLE>, int tb) {
       const int t = tb + J;
       const double v = pre[J];
-      if constexpr (WHOLE) pre[J] = sample(2 * R + (t + W < len ? t + W : len - 1));  // same step of the next block
+      if (WHOLE || t + W < len) pre[J] = sample(2 * R + t + W);  // same step of the next block
       win[(J + 2 * R) % W] = v;
       if (WHOLE || t < len) {
         double g = 0.0, d = 0.0;
@@ -111,8 +115,9 @@ __device__ __forceinline__ void strided_block(const StridedGeo& p, const Taps& w
       (step(std::integral_constant<int, J>{}, whole, tb), ...);
     };
     int tb = 0;
-    for (; tb + W <= len; tb += W) block(std::true_type{}, tb, std::make_integer_sequence<int, W>{});
-    if (tb < len) block(std::false_type{}, tb, std::make_integer_sequence<int, W>{});  // what is left
+    for (; tb + 2 * W <= len; tb += W) block(std::true_type{}, tb, std::make_integer_sequence<int, W>{});
+#pragma unroll 1
+    for (; tb < len; tb += W) block(std::false_type{}, tb, std::make_integer_sequence<int, W>{});  // what is left
   };
   if constexpr (MASKED) {
     CellRuns runs(p.cells + o / 8 * p.cell_other + xt, p.cell_axis, c0, clen);

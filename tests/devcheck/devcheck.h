@@ -6,6 +6,8 @@
 // defines the lane index and the ballot.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -37,3 +39,11 @@ inline float __builtin_amdgcn_sqrtf(float a) { return std::sqrt(a); }
 
 unsigned __lane_id();
 unsigned long long __ballot(int predicate);
+
+// kernels and their launches only have to parse
+#undef __global__
+#define __global__
+#undef __launch_bounds__
+#define __launch_bounds__(...)
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(...) ((void)0)

@@ -34,3 +34,7 @@ def test_ties_between_equal_cross_products(tmp_path):
 
 def test_e3_is_of_unit_length_in_float64(tmp_path):
     _run("eigen_unit", tmp_path)
+
+
+def test_integration_pieces_load_each_sample_once(tmp_path):
+    _run("strided_loads", tmp_path)
