@@ -1,0 +1,203 @@
+// What the library's host code plans for masked volumes, split passes and the
+// re-angling call, checked without a GPU (see hostcheck.h).  The launch functions
+// of stub_kernels.cpp are wrapped at link time (--wrap): the checks here come
+// first, then that file's own.  One group of checks per run, named by the first
+// argument; prints "plans: OK" and exits 0 when all hold.
+#include <algorithm>
+#include <climits>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "hostcheck.h"
+#include "st.h"
+#include "st_host.h"
+#include "st_internal.h"
+#include "st_surrogate.h"
+
+namespace {
+
+int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// the outputs of the call under way, and what its launches said
+struct Buffer { const char* p; size_t bytes; };
+std::vector<Buffer> g_outputs;
+int64_t g_n = 0;
+int g_masked_grads = 0, g_masked_strided = 0, g_masked_layers = 0, g_angles = 0;
+const uint8_t* g_tables[3] = {nullptr, nullptr, nullptr};  // y, z, grad of the last gradient launch
+int64_t g_table_len = 0;
+int g_reach = 0;
+
+bool inside_outputs(const void* p, size_t bytes) {
+  for (const Buffer& b : g_outputs)
+    if (p >= b.p && static_cast<const char*>(p) + bytes <= b.p + b.bytes) return true;
+  return false;
+}
+
+}  // namespace
+
+namespace st {
+
+#define ST_PAIR(ret, name, mangled, args)                   \
+  ret real_##name args asm("__real_" mangled);              \
+  ret wrap_##name args asm("__wrap_" mangled);
+ST_PAIR(hipError_t, grad, "_ZN2st17launch_grad_fusedEiiRKNS_15GradFusedParamsEP12ihipStream_t",
+        (int R, int in_dtype, const GradFusedParams& p, hipStream_t stream))
+ST_PAIR(hipError_t, strided, "_ZN2st14launch_stridedEiibRKNS_13StridedParamsEP12ihipStream_t",
+        (int R, int in_dtype, bool with_d, const StridedParams& p, hipStream_t stream))
+ST_PAIR(hipError_t, conv, "_ZN2st14launch_sg_convEiiRKNS_12SgConvParamsEP12ihipStream_t",
+        (int layer, int dtype, const SgConvParams& p, hipStream_t stream))
+ST_PAIR(hipError_t, angles, "_ZN2st13launch_anglesERKNS_12AnglesParamsEP12ihipStream_t",
+        (const AnglesParams& p, hipStream_t stream))
+#undef ST_PAIR
+
+hipError_t wrap_grad(int R, int in_dtype, const GradFusedParams& p, hipStream_t stream) {
+  if (p.cells != nullptr) {
+    ++g_masked_grads;
+    const MaskCells& c = p.mask;
+    const int64_t cz = cells_of(p.nz), cy = cells_of(p.ny), cx = cells_of(p.nx), xs = cdiv(p.nx, 64);
+    const int64_t n = p.nz * p.ny * p.nx, table = cz * cy * xs;
+    if (c.mask == nullptr) hc::violation("mask cells without a mask");
+    hc::need(c.mask, static_cast<size_t>(n), "mask");
+    const size_t bytes = static_cast<size_t>(mask_cell_bytes(p.nz, p.ny, p.nx));
+    hc::need(c.base, bytes, "mask cells");
+    if (!inside_outputs(c.base, bytes)) hc::violation("the mask cells do not lie in an output of the call");
+    if (c.y != c.base + cz * cy * cx || c.z != c.y + table || c.grad != c.z + table ||
+        c.grad + table != c.base + bytes)
+      hc::violation("the cell tables overlap or leave their bytes");
+    if (p.cells != c.grad) hc::violation("the gradient pass reads another table");
+    if (p.x_tiles != xs || (p.rows != 4 && p.rows != 8)) hc::violation("cells of other tiles than the gradient's");
+    g_tables[0] = c.y; g_tables[1] = c.z; g_tables[2] = c.grad;
+    g_table_len = table;
+    g_reach = c.reach;
+  } else {
+    g_tables[0] = g_tables[1] = g_tables[2] = nullptr;
+  }
+  return real_grad(R, in_dtype, p, stream);
+}
+
+hipError_t wrap_strided(int R, int in_dtype, bool with_d, const StridedParams& p, hipStream_t stream) {
+  if (p.cells != nullptr) {
+    ++g_masked_strided;
+    const bool zaxis = p.s_axis > p.s_other;
+    if (with_d || in_dtype != ST_DTYPE_F32 || p.so_axis != p.s_axis || p.so_other != p.s_other)
+      hc::violation("cells given to a pass that does without");
+    if (p.cells != g_tables[zaxis ? 1 : 0]) hc::violation("the %c integration reads another table", zaxis ? 'z' : 'y');
+    if (R != g_reach) hc::violation("cells dilated by %d for an integration of radius %d", g_reach, R);
+    const int64_t xs = cdiv(p.nx, 64), cy = cells_of(zaxis ? p.n_other : p.n_axis);
+    const int64_t za = cy * xs, ya = xs;  // strides of a cell along z and y
+    if (p.cell_axis != (zaxis ? za : ya) || p.cell_other != (zaxis ? ya : za)) hc::violation("cell strides");
+    const int64_t last = (cells_of(p.n_axis) - 1) * p.cell_axis + (cells_of(p.n_other) - 1) * p.cell_other + xs - 1;
+    if (last + 1 != g_table_len) hc::violation("cell indices reach %lld of %lld", (long long)last, (long long)g_table_len);
+  }
+  return real_strided(R, in_dtype, with_d, p, stream);
+}
+
+hipError_t wrap_conv(int layer, int dtype, const SgConvParams& p, hipStream_t stream) {
+  static bool built = false;
+  if (layer == 1 && p.z_lo == 0) built = false;
+  if (p.cells != nullptr) {
+    ++g_masked_layers;
+    if (p.mask == nullptr) hc::violation("cells without a mask");
+    hc::need(p.mask, static_cast<size_t>(p.n), "mask");
+    hc::need(p.cells, static_cast<size_t>(sg_cells(p.nz) * sg_cells(p.ny) * sg_cells(p.nx)), "surrogate mask cells");
+    if (p.reach != kSgLayers - layer) hc::violation("layer %d reaches %d voxels", layer, p.reach);
+    if (layer == 1 && p.build_cells) built = true;
+    if (!built) hc::violation("layer %d reads cells that no launch made", layer);
+  }
+  return real_conv(layer, dtype, p, stream);
+}
+
+hipError_t wrap_angles(const AnglesParams& p, hipStream_t stream) {
+  ++g_angles;
+  if (p.n < 1 || p.n >= (int64_t(1) << 51) || cdiv(p.n, 1024) > INT32_MAX) hc::violation("k_angles: grid");
+  if (p.vec_ok) {  // a lane's four voxels in one access
+    if (p.n % 4 != 0) hc::violation("k_angles: 16-byte accesses to planes of %lld", (long long)p.n);
+    for (const void* q : {(const void*)p.e3, (const void*)p.ha, (const void*)p.ia})
+      if (reinterpret_cast<uintptr_t>(q) % 16) hc::violation("k_angles: 16-byte accesses to an unaligned buffer");
+    for (const void* q : {(const void*)p.mask, (const void*)p.flags})
+      if (reinterpret_cast<uintptr_t>(q) % 4) hc::violation("k_angles: 4-byte accesses to an unaligned buffer");
+  }
+  return real_angles(p, stream);
+}
+
+}  // namespace st
+
+namespace {
+
+void expect(int got, int want, const char* what) {
+  if (got != want) {
+    std::fprintf(stderr, "plans FAIL: %s returned %d, expected %d (%s)\n", what, got, want, st_last_error());
+    std::exit(1);
+  }
+}
+
+void* dev(size_t bytes) {
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess || p == nullptr) {
+    std::fprintf(stderr, "plans FAIL: stub allocation of %zu bytes\n", bytes);
+    std::exit(1);
+  }
+  return p;
+}
+
+const double kC[3] = {10.5, 11.25, 19.5}, kD[3] = {1.0, 0.2, -0.1};
+
+// One masked st_compute with a caller workspace and the outputs whose letters are
+// in `which` (e: e3, v: evals, f: fa, h: ha, i: ia, b: flags).
+void masked_call(int64_t nz, int64_t ny, int64_t nx, double sigma, double rho, const char* which, bool mask = true) {
+  const int64_t n = nz * ny * nx;
+  void* vol = dev(static_cast<size_t>(n) * 2);
+  uint8_t* m = mask ? static_cast<uint8_t*>(dev(static_cast<size_t>(n))) : nullptr;
+  g_outputs.clear();
+  g_n = n;
+  auto out = [&](char k, size_t bytes) -> void* {
+    if (std::strchr(which, k) == nullptr) return nullptr;
+    void* p = dev(bytes);
+    g_outputs.push_back(Buffer{static_cast<const char*>(p), bytes});
+    return p;
+  };
+  const size_t N = static_cast<size_t>(n);
+  float* e3 = static_cast<float*>(out('e', 12 * N));
+  float* ev = static_cast<float*>(out('v', 12 * N));
+  float* fa = static_cast<float*>(out('f', 4 * N));
+  float* ha = static_cast<float*>(out('h', 4 * N));
+  float* ia = static_cast<float*>(out('i', 4 * N));
+  uint8_t* fl = static_cast<uint8_t*>(out('b', N));
+  const size_t wsb = st_workspace_bytes(nz, ny, nx);
+  void* ws = dev(wsb);
+  expect(st_compute(vol, ST_DTYPE_U16, m, nz, ny, nx, sigma, rho, 4.0, kC, kD, e3, ev, fa, ha, ia, fl, ws, wsb,
+                    nullptr),
+         ST_OK, "st_compute");
+  for (void* p : {vol, (void*)m, (void*)e3, (void*)ev, (void*)fa, (void*)ha, (void*)ia, (void*)fl, ws}) (void)hipFree(p);
+}
+
+// A mask's cells are made from 2^23 voxels on, for the fused gradient.
+void threshold() {
+  struct Case { int64_t nz, ny, nx; double sigma; bool mask; int cells; };
+  for (const Case& c : {Case{162, 162, 162, 1.0, true, 0}, Case{127, 256, 256, 1.0, true, 0},
+                        Case{128, 256, 256, 1.0, true, 1}, Case{128, 256, 256, 1.0, false, 0},
+                        Case{128, 256, 256, 2.6, true, 0}}) {
+    g_masked_grads = g_masked_strided = 0;
+    masked_call(c.nz, c.ny, c.nx, c.sigma, 2.0, "b", c.mask);
+    if (g_masked_grads != c.cells || g_masked_strided != 2 * c.cells)
+      hc::violation("%lld x %lld x %lld, sigma %g: %d masked gradient launches, expected %d", (long long)c.nz,
+                    (long long)c.ny, (long long)c.nx, c.sigma, g_masked_grads, c.cells);
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "threshold") threshold();
+  else return 2;
+  if (hc::live_objects() != 0) {
+    std::printf("plans: FAIL (objects leaked)\n");
+    return 1;
+  }
+  std::printf("plans: OK\n");
+  return 0;
+}
