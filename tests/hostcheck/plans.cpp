@@ -188,11 +188,37 @@ void threshold() {
   }
 }
 
+// One masked st_surrogate_infer in z slabs of `slab` planes; layers with cells.
+int surrogate_call(int64_t nz, int64_t ny, int64_t nx, int64_t slab, double min_confidence) {
+  const int64_t n = nz * ny * nx;
+  const size_t N = static_cast<size_t>(n);
+  setenv("ST_SURROGATE_SLAB_BYTES", std::to_string(2 * (slab + 8) * ny * nx * 64).c_str(), 1);
+  void* vol = dev(2 * N);
+  uint8_t* m = static_cast<uint8_t*>(dev(N));
+  float* w = static_cast<float*>(dev(4 * ST_SURROGATE_WEIGHTS));
+  float* fa = static_cast<float*>(dev(4 * N));
+  g_masked_layers = 0;
+  expect(st_surrogate_infer(vol, ST_DTYPE_U16, m, nz, ny, nx, w, 4 * ST_SURROGATE_WEIGHTS, min_confidence, 1.0, 2.0, 4.0,
+                            kC, kD, nullptr, fa, nullptr, nullptr, nullptr, nullptr),
+         ST_OK, "st_surrogate_infer");
+  for (void* p : {vol, (void*)m, (void*)w, (void*)fa}) (void)hipFree(p);
+  unsetenv("ST_SURROGATE_SLAB_BYTES");
+  return g_masked_layers;
+}
+
+// The surrogate makes its own from 2^23 voxels on, too.
+void surrogate_threshold() {
+  if (surrogate_call(128, 128, 128, 32, 0.0) != 0) hc::violation("cells for 128^3");
+  if (surrogate_call(127, 256, 256, 32, 0.0) != 0) hc::violation("cells below 2^23 voxels");
+  if (surrogate_call(128, 256, 256, 32, 0.0) != 4 * 5) hc::violation("no cells at 2^23 voxels in four slabs");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "threshold") threshold();
+  else if (what == "surrogate_threshold") surrogate_threshold();
   else return 2;
   if (hc::live_objects() != 0) {
     std::printf("plans: FAIL (objects leaked)\n");

@@ -56,3 +56,7 @@ def _run(exe, group):
 
 def test_mask_cells_only_where_they_pay(plans):
     _run(plans, "threshold")
+
+
+def test_surrogate_mask_cells_only_where_they_pay(plans):
+    _run(plans, "surrogate_threshold")
