@@ -34,7 +34,8 @@ struct CellRuns {
   __device__ __forceinline__ void look() {
     const int k = c + static_cast<int>(__lane_id());
     const uint64_t b = __ballot(8 * k < end && cells[(8 * k < end ? k : c) * stride] != 0);
-    bits = b | (((b << 1) | (b << 2)) & ((b >> 1) | (b >> 2)));
+    const uint64_t two = (b << 1) & (b >> 2);  // first cell of a gap of two (or the cell after a marked one)
+    bits = b | ((b << 1) & (b >> 1)) | two | (two << 1);
   }
   __device__ __forceinline__ CellRuns(const uint8_t* cells_, int64_t stride_, int a_, int len)
       : cells(cells_), stride(stride_), a(a_), end(a_ + len), c(a_ / 8) {

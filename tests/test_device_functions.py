@@ -38,3 +38,7 @@ def test_e3_is_of_unit_length_in_float64(tmp_path):
 
 def test_integration_pieces_load_each_sample_once(tmp_path):
     _run("strided_loads", tmp_path)
+
+
+def test_runs_of_marked_cells(tmp_path):
+    _run("cell_runs", tmp_path, "-pthread")
