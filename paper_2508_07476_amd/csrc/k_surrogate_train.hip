@@ -49,9 +49,9 @@ __global__ void k_sg_pack_bwd(const float* blob, __bf16* w25t) {
 // a voxel) and the per-voxel chain; one thread per sum walking the block's voxels
 // in LDS, as before, took 128 us for 2^20 voxels, against 66.
 __global__ __launch_bounds__(256) void k_sg_head_train(const SgHeadParams p) {
-  constexpr int DQ = 16, DS = 13;  // rows of the product (11 quantities, the rest unused), row length in LDS
+  constexpr int DS = kSgHeadRow;
   __shared__ __bf16 xs[256][C + 2];
-  __shared__ float ds[256 * DS + DQ];
+  __shared__ float ds[256 * DS];
   // the head's weights by channel, read by every lane at once: as scalars the
   // 160 do not fit the scalar registers and are loaded anew for every voxel
   __shared__ __attribute__((aligned(16))) float hw[C][8];
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void k_sg_head_train(const SgHeadParams p) {
 #pragma unroll
   for (int n = 0; n < 3; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (tid < 5 * C) hw[tid % C][tid / C] = p.head_w[tid];
-  for (int i = tid; i < 256 * DS + DQ; i += 256) ds[i] = 0.f;
+  for (int i = tid; i < 256 * DS; i += 256) ds[i] = 0.f;
   __syncthreads();
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * 256; base < p.n;
        base += static_cast<int64_t>(gridDim.x) * 256) {  // block-uniform trip count
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void k_sg_head_train(const SgHeadParams p) {
 #pragma unroll
     for (int c = 0; c < C; ++c) xs[tid][c] = x8[c / 8][c % 8];
 #pragma unroll
-    for (int k = 0; k < 11; ++k) ds[tid * DS + k] = d[k];
+    for (int k = 0; k < 11; ++k) ds[sg_head_place(tid, k)] = d[k];
     // the wave reads only its own lanes' rows
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void k_sg_head_train(const SgHeadParams p) {
 #pragma unroll 4
     for (int i = 0; i < 16; ++i) {
       const int row = 64 * wave + 4 * i + lk;
-      const float a = ds[row * DS + li];  // li > 10: a product row that is not used
+      const float a = ds[sg_head_place(row, li)];  // li > 10: a product row that is not used
       acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, static_cast<float>(xs[row][li]), acc[0], 0, 0, 0);
       acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, static_cast<float>(xs[row][16 + li]), acc[1], 0, 0, 0);
       acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, 1.f, acc[2], 0, 0, 0);
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void k_sg_head_train(const SgHeadParams p) {
   // the four waves' sums, added in wave order
   __syncthreads();
   float* part = ds;  // [4][3][16][16]
-  static_assert(4 * 3 * 256 <= 256 * DS + DQ, "the waves' sums fit");
+  static_assert(4 * 3 * 256 <= 256 * DS, "the waves' sums fit");
 #pragma unroll
   for (int n = 0; n < 3; ++n)
 #pragma unroll

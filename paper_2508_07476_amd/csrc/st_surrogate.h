@@ -165,6 +165,14 @@ inline int64_t sg_wgrad_planes(int64_t nz, int64_t ny) {
   return (nz + chunks - 1) / chunks;
 }
 constexpr int kSgHeadSums = 5 * kSgChannels + 5 + 6;  // head gradient (Wh, bh) and six loss sums
+// The 11 quantities of a voxel that the head's products take lie in LDS rows of 13
+// (the last two zero).  Place of quantity q in row r of the block: a product has 16
+// rows, and the five past the quantities are read as zeros of the lane's own row,
+// since the next rows may be another wave's, which writes them at the time.
+constexpr int kSgHeadRow = 13;
+constexpr __host__ __device__ int sg_head_place(int r, int q) {
+  return r * kSgHeadRow + (q < kSgHeadRow ? q : kSgHeadRow - 1);
+}
 constexpr int kSgTrainStats = 8;          // dir, fa, conf, total loss, sum w, within, mean angle (deg), count
 
 // Backward weights of layers 2..5, packed [layer - 2][tap'][co'][ci'] = W[ci'][co'][26 - tap'].

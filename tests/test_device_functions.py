@@ -42,3 +42,7 @@ def test_integration_pieces_load_each_sample_once(tmp_path):
 
 def test_runs_of_marked_cells(tmp_path):
     _run("cell_runs", tmp_path, "-pthread")
+
+
+def test_head_products_read_the_waves_own_rows(tmp_path):
+    _run("head_places", tmp_path)
