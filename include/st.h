@@ -346,8 +346,8 @@ int st_batch_tune(st_batch* batch, void* stream, int reps);
 /* Current configuration; any output pointer may be NULL.  lanes: chains in use;
  * use_graph: 1 if launches replay the captured graph; grad_min_blocks: the
  * blocks of four waves (one wave per tile row) that fill the part of the chip the
- * gradient pass splits z for; strided_min_waves: the waves the integration
- * passes split for (with more than one chain both are a quarter of a lone
+ * gradient pass splits z for (1024 and above: the whole chip); strided_min_waves:
+ * the waves the integration passes split for (with more than one chain both are a quarter of a lone
  * st_compute's, since the chains fill the chip together); best_ms: the tuned
  * time per launch of the configuration st_batch_tune chose (0 before tuning). */
 int st_batch_config(const st_batch* batch, int* lanes, int* use_graph, int64_t* grad_min_blocks,

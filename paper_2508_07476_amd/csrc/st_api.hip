@@ -405,9 +405,9 @@ void plan_path(const PathArgs& a, char* ws, const LaunchShape& shape, PathPlan* 
     p.rows = static_cast<int>(rows);
     p.y_tiles = (ny + rows - 1) / rows;
     // grad_min_blocks counts blocks of four waves, four to a compute unit
-    const int64_t cus = std::max<int64_t>(1, shape.grad_min_blocks / 4);
+    const int64_t cus = std::min<int64_t>(256, std::max<int64_t>(1, shape.grad_min_blocks / 4));
     const int64_t nch = grad_pieces(p.x_tiles * p.y_tiles, nz, ps, cus, rows == 8 ? 2 : ps <= 5 ? 4 : 3,
-                                    cus >= 256);
+                                    shape.alone);
     p.chunk = (nz + nch - 1) / nch;
     p.nchunks = static_cast<int>((nz + p.chunk - 1) / p.chunk);
     p.wg = gs; p.wd = ds;

@@ -138,6 +138,7 @@ st::host::LaunchShape chunk_shape(const st_batch* b, int i) {
   st::host::LaunchShape s = b->shape;
   s.grad_rows = b->tiles[i].grad_rows;
   s.xfinal_lanes = b->tiles[i].xfinal_lanes;
+  s.alone = b->lanes == 1 && !b->grouped;
   return s;
 }
 
@@ -187,6 +188,7 @@ int plan_grouped(st_batch* b) {
       const int i = rd.chunk_off[k].first;
       st::host::LaunchShape sh = chunk_shape(b, i);
       const double share = static_cast<double>(b->chunks[i].n) / static_cast<double>(rd.voxels);
+      sh.alone = rd.chunk_off.size() == 1;
       sh.grad_min_blocks = std::max<int64_t>(1, static_cast<int64_t>(base.grad_min_blocks * share));
       sh.strided_min_waves = std::max<int64_t>(1, static_cast<int64_t>(base.strided_min_waves * share));
       st::host::plan_path(b->chunks[i], b->ws + rd.chunk_off[k].second, sh, &plans[k]);

@@ -41,9 +41,10 @@ struct PathArgs {
 
 // Launch shapes: how far each pass splits its filtered axis to fill the chip.
 // grad_min_blocks: blocks of four gradient waves that fill the compute units the
-// launch has for itself (1024: the chip); the pass splits z where that shortens
-// the launch (every piece filters 2R halo planes again, so a 512^3 volume, whose
-// x-y tiles fill the chip, stays whole).  The strided passes split until they
+// launch has for itself (1024, and anything above: the chip); the pass splits z
+// where that shortens the launch (every piece filters 2R halo planes again, so a
+// 512^3 volume, whose x-y tiles fill the chip, stays whole).  alone: no other launch
+// runs beside it, so that its fullest unit ends it.  The strided passes split until they
 // have at least strided_min_waves waves while the pieces stay long against the
 // filter radius, and down to pieces of about the radius until they have a quarter
 // of that.  A batch of concurrent chains uses a quarter of both targets.
@@ -56,6 +57,7 @@ struct LaunchShape {
   int64_t strided_min_waves = 16384;
   int grad_rows = 0;
   int xfinal_lanes = 0;
+  bool alone = true;
 };
 
 // Sizes each in [1, 2^31) with every byte count of the path fitting: *n is the

@@ -29,6 +29,7 @@ int g_masked_grads = 0, g_masked_strided = 0, g_masked_layers = 0, g_angles = 0;
 const uint8_t* g_tables[3] = {nullptr, nullptr, nullptr};  // y, z, grad of the last gradient launch
 int64_t g_table_len = 0;
 int g_reach = 0;
+std::vector<int> g_grad_pieces;  // z pieces of the gradient launches, chunk by chunk
 
 bool inside_outputs(const void* p, size_t bytes) {
   for (const Buffer& b : g_outputs)
@@ -45,6 +46,8 @@ namespace st {
   ret wrap_##name args asm("__wrap_" mangled);
 ST_PAIR(hipError_t, grad, "_ZN2st17launch_grad_fusedEiiRKNS_15GradFusedParamsEP12ihipStream_t",
         (int R, int in_dtype, const GradFusedParams& p, hipStream_t stream))
+ST_PAIR(hipError_t, grouped, "_ZN2st25launch_grad_fused_groupedEiiiRKNS_14GradFusedGroupElP12ihipStream_t",
+        (int R, int in_dtype, int rows, const GradFusedGroup& p, int64_t blocks, hipStream_t stream))
 ST_PAIR(hipError_t, strided, "_ZN2st14launch_stridedEiibRKNS_13StridedParamsEP12ihipStream_t",
         (int R, int in_dtype, bool with_d, const StridedParams& p, hipStream_t stream))
 ST_PAIR(hipError_t, conv, "_ZN2st14launch_sg_convEiiRKNS_12SgConvParamsEP12ihipStream_t",
@@ -54,6 +57,7 @@ ST_PAIR(hipError_t, angles, "_ZN2st13launch_anglesERKNS_12AnglesParamsEP12ihipSt
 #undef ST_PAIR
 
 hipError_t wrap_grad(int R, int in_dtype, const GradFusedParams& p, hipStream_t stream) {
+  g_grad_pieces.push_back(p.nchunks);
   if (p.cells != nullptr) {
     ++g_masked_grads;
     const MaskCells& c = p.mask;
@@ -76,6 +80,11 @@ hipError_t wrap_grad(int R, int in_dtype, const GradFusedParams& p, hipStream_t 
     g_tables[0] = g_tables[1] = g_tables[2] = nullptr;
   }
   return real_grad(R, in_dtype, p, stream);
+}
+
+hipError_t wrap_grouped(int R, int in_dtype, int rows, const GradFusedGroup& p, int64_t blocks, hipStream_t stream) {
+  for (int e = 0; e < p.g.count; ++e) g_grad_pieces.push_back(p.g.geo[e].nchunks);
+  return real_grouped(R, in_dtype, rows, p, blocks, stream);
 }
 
 hipError_t wrap_strided(int R, int in_dtype, bool with_d, const StridedParams& p, hipStream_t stream) {
@@ -213,12 +222,77 @@ void surrogate_threshold() {
   if (surrogate_call(128, 256, 256, 32, 0.0) != 4 * 5) hc::violation("no cells at 2^23 voxels in four slabs");
 }
 
+// z pieces of the gradient pass for a launch shape.
+int pieces(int64_t nz, int64_t ny, int64_t nx, double sigma, const st::host::LaunchShape& shape) {
+  static uint16_t vol[1];
+  static float out[1];
+  st::host::PathArgs a;
+  expect(st::host::prepare_path(a, vol, ST_DTYPE_U16, nullptr, nz, ny, nx, sigma, 2.0, 4.0, nullptr, nullptr, nullptr,
+                                nullptr, out, nullptr, nullptr, nullptr),
+         ST_OK, "prepare_path");
+  st::host::PathPlan plan;
+  st::host::plan_path(a, reinterpret_cast<char*>(uintptr_t(1) << 32), shape, &plan);  // addresses only
+  return plan.grad.nchunks;
+}
+
+// How far the gradient pass splits z: a target above the chip plans for the chip,
+// and whether a launch has it for itself is said, not taken from the target.
+void split() {
+  const int64_t sizes[][3] = {{64, 64, 64}, {120, 90, 200}, {48, 300, 300}, {200, 40, 333}, {90, 512, 512}, {33, 65, 700}};
+  int differ = 0;
+  for (const auto& q : sizes)
+    for (double sigma : {1.0, 1.5, 2.0}) {
+      st::host::LaunchShape chip, more, beside;
+      more.grad_min_blocks = 4 * chip.grad_min_blocks;
+      beside.alone = false;
+      const int n = pieces(q[0], q[1], q[2], sigma, chip);
+      if (pieces(q[0], q[1], q[2], sigma, more) != n)
+        hc::violation("%lld x %lld x %lld, sigma %g: %d pieces for four chips, %d for one", (long long)q[0],
+                      (long long)q[1], (long long)q[2], sigma, pieces(q[0], q[1], q[2], sigma, more), n);
+      differ += pieces(q[0], q[1], q[2], sigma, beside) != n;
+    }
+  if (differ == 0) hc::violation("a launch beside others is planned as one alone");
+  // chains: two chunks in one chain have the chip one after the other, in two beside
+  // each other; grouped: one chunk has it, two share it
+  const int64_t N = 64 * 64 * 64;
+  std::vector<st_chunk> chunks(2);
+  for (st_chunk& c : chunks) {
+    c = st_chunk{};
+    c.volume = dev(2 * N); c.dtype = ST_DTYPE_U16;
+    c.nz = c.ny = c.nx = 64; c.rho = 2.0;
+    c.fa = static_cast<float*>(dev(4 * N));
+  }
+  auto batch_pieces = [&](int count, int lanes) {
+    g_grad_pieces.clear();
+    st_batch* b = nullptr;
+    expect(st_batch_create(chunks.data(), count, 1.0, 4.0, nullptr, nullptr, lanes, nullptr, 0, &b), ST_OK,
+           "st_batch_create");
+    expect(st_batch_destroy(b), ST_OK, "st_batch_destroy");
+    return g_grad_pieces;
+  };
+  st::host::LaunchShape chip, quarter, half;
+  quarter.grad_min_blocks = chip.grad_min_blocks / 4;
+  half.grad_min_blocks = chip.grad_min_blocks / 2;
+  quarter.alone = half.alone = false;
+  const std::vector<int> one(2, pieces(64, 64, 64, 1.0, chip)), two(2, pieces(64, 64, 64, 1.0, quarter));
+  if (batch_pieces(2, 1) != one) hc::violation("one chain: not planned as alone");
+  if (batch_pieces(2, 2) != two) hc::violation("two chains: planned otherwise than beside each other");
+  if (batch_pieces(1, ST_BATCH_GROUPED) != std::vector<int>(1, one[0])) hc::violation("a grouped round of one chunk");
+  if (batch_pieces(2, ST_BATCH_GROUPED) != std::vector<int>(2, pieces(64, 64, 64, 1.0, half)))
+    hc::violation("a grouped round of two chunks");
+  for (st_chunk& c : chunks) {
+    (void)hipFree(const_cast<void*>(c.volume));
+    (void)hipFree(c.fa);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "threshold") threshold();
   else if (what == "surrogate_threshold") surrogate_threshold();
+  else if (what == "split") split();
   else return 2;
   if (hc::live_objects() != 0) {
     std::printf("plans: FAIL (objects leaked)\n");

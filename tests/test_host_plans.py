@@ -16,7 +16,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, os.path.join(ROOT, "tests", "hostcheck"))
 
-WRAPPED = re.compile(r"\bT (_ZN2st\d+launch_(?:grad_fused|strided|sg_conv|angles)E\w+)")
+WRAPPED = re.compile(r"\bT (_ZN2st\d+launch_(?:grad_fused|grad_fused_grouped|strided|sg_conv|angles)E\w+)")
 
 
 @pytest.fixture(scope="module")
@@ -38,7 +38,7 @@ def plans(tmp_path_factory):
     subprocess.run([hc.tool("clang"), "-c", blobs, "-o", blobs[:-2] + ".o"], check=True, capture_output=True)
     stubs = subprocess.run([hc.tool("nm"), os.path.join(out, "stub_kernels.o")], capture_output=True, text=True, check=True)
     wraps = [f"-Wl,--wrap={s}" for s in WRAPPED.findall(stubs.stdout)]
-    assert len(wraps) == 4
+    assert len(wraps) == 5
     exe = os.path.join(out, "plans")
     r = subprocess.run([hc.tool("clang++"), "-fsanitize=address,undefined", *wraps, *objs, blobs[:-2] + ".o", "-o", exe],
                        capture_output=True, text=True)
@@ -60,3 +60,7 @@ def test_mask_cells_only_where_they_pay(plans):
 
 def test_surrogate_mask_cells_only_where_they_pay(plans):
     _run(plans, "surrogate_threshold")
+
+
+def test_gradient_split_targets(plans):
+    _run(plans, "split")
