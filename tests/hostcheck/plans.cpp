@@ -24,14 +24,15 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // the outputs of the call under way, and what its launches said
 struct Buffer { const char* p; size_t bytes; };
 std::vector<Buffer> g_outputs;
-int64_t g_n = 0;
 int g_masked_grads = 0, g_masked_strided = 0, g_masked_layers = 0, g_angles = 0;
 const uint8_t* g_tables[3] = {nullptr, nullptr, nullptr};  // y, z, grad of the last gradient launch
 int64_t g_table_len = 0;
-int g_reach = 0;
+int g_reach = 0, g_wide_angles = 0, g_since_grad = 0;
+bool g_any_output = false;  // outputs that the library allocates itself
 std::vector<int> g_grad_pieces;  // z pieces of the gradient launches, chunk by chunk
 
 bool inside_outputs(const void* p, size_t bytes) {
+  if (g_any_output) return true;
   for (const Buffer& b : g_outputs)
     if (p >= b.p && static_cast<const char*>(p) + bytes <= b.p + b.bytes) return true;
   return false;
@@ -58,6 +59,7 @@ ST_PAIR(hipError_t, angles, "_ZN2st13launch_anglesERKNS_12AnglesParamsEP12ihipSt
 
 hipError_t wrap_grad(int R, int in_dtype, const GradFusedParams& p, hipStream_t stream) {
   g_grad_pieces.push_back(p.nchunks);
+  g_since_grad = 0;
   if (p.cells != nullptr) {
     ++g_masked_grads;
     const MaskCells& c = p.mask;
@@ -90,10 +92,10 @@ hipError_t wrap_grouped(int R, int in_dtype, int rows, const GradFusedGroup& p, 
 hipError_t wrap_strided(int R, int in_dtype, bool with_d, const StridedParams& p, hipStream_t stream) {
   if (p.cells != nullptr) {
     ++g_masked_strided;
-    const bool zaxis = p.s_axis > p.s_other;
+    const bool zaxis = g_since_grad++ == 0;  // z, then y
     if (with_d || in_dtype != ST_DTYPE_F32 || p.so_axis != p.s_axis || p.so_other != p.s_other)
       hc::violation("cells given to a pass that does without");
-    if (p.cells != g_tables[zaxis ? 1 : 0]) hc::violation("the %c integration reads another table", zaxis ? 'z' : 'y');
+    if (p.cells != g_tables[zaxis ? 1 : 0]) hc::violation("the %c integration of %lld x %lld x %lld reads another table", zaxis ? 'z' : 'y', (long long)p.n_axis, (long long)p.n_other, (long long)p.nx);
     if (R != g_reach) hc::violation("cells dilated by %d for an integration of radius %d", g_reach, R);
     const int64_t xs = cdiv(p.nx, 64), cy = cells_of(zaxis ? p.n_other : p.n_axis);
     const int64_t za = cy * xs, ya = xs;  // strides of a cell along z and y
@@ -122,6 +124,7 @@ hipError_t wrap_conv(int layer, int dtype, const SgConvParams& p, hipStream_t st
 hipError_t wrap_angles(const AnglesParams& p, hipStream_t stream) {
   ++g_angles;
   if (p.n < 1 || p.n >= (int64_t(1) << 51) || cdiv(p.n, 1024) > INT32_MAX) hc::violation("k_angles: grid");
+  g_wide_angles += p.vec_ok != 0;
   if (p.vec_ok) {  // a lane's four voxels in one access
     if (p.n % 4 != 0) hc::violation("k_angles: 16-byte accesses to planes of %lld", (long long)p.n);
     for (const void* q : {(const void*)p.e3, (const void*)p.ha, (const void*)p.ia})
@@ -161,7 +164,6 @@ void masked_call(int64_t nz, int64_t ny, int64_t nx, double sigma, double rho, c
   void* vol = dev(static_cast<size_t>(n) * 2);
   uint8_t* m = mask ? static_cast<uint8_t*>(dev(static_cast<size_t>(n))) : nullptr;
   g_outputs.clear();
-  g_n = n;
   auto out = [&](char k, size_t bytes) -> void* {
     if (std::strchr(which, k) == nullptr) return nullptr;
     void* p = dev(bytes);
@@ -286,6 +288,85 @@ void split() {
   }
 }
 
+// Where the cells of masked calls lie: in the first output asked for, whichever that
+// is and however few bytes it has (flags: one a voxel), for thin shapes and sizes on
+// and off the cells' edges, or nowhere if they would not fit; of a chunk batch's
+// chunks each in its own outputs; of the surrogate's in its own scratch, in slabs and
+// with the whole-volume fallback.
+void cells() {
+  const int64_t sizes[][3] = {{128, 256, 256}, {129, 251, 263}, {9, 1000, 1000}, {1000, 1000, 9}, {65, 8, 17000}};
+  for (const auto& q : sizes)
+    for (const char* which : {"b", "f", "vb"}) {
+      g_masked_grads = g_masked_strided = 0;
+      masked_call(q[0], q[1], q[2], 1.0, 2.0, which);
+      if (g_masked_grads != 1 || g_masked_strided != 2) hc::violation("a masked call without cells");
+    }
+  masked_call(int64_t(1) << 23, 1, 1, 1.0, 2.0, "b");  // a column: half a byte of cells a voxel
+  // chains and grouped rounds
+  const int64_t nz = 128, ny = 256, nx = 257, N = nz * ny * nx;
+  std::vector<st_chunk> chunks(3);
+  g_outputs.clear();
+  for (size_t i = 0; i < chunks.size(); ++i) {
+    st_chunk& c = chunks[i];
+    c = st_chunk{};
+    c.volume = dev(2 * N); c.dtype = ST_DTYPE_U16;
+    if (i != 1) c.mask = static_cast<uint8_t*>(dev(N));
+    c.nz = nz; c.ny = ny; c.nx = nx; c.rho = 2.0;
+    c.flags = static_cast<uint8_t*>(dev(N));
+    g_outputs.push_back(Buffer{reinterpret_cast<const char*>(c.flags), static_cast<size_t>(N)});
+  }
+  for (int lanes : {1, 2, ST_BATCH_GROUPED}) {
+    g_masked_grads = 0;
+    const size_t wsb = st_batch_workspace_bytes(chunks.data(), 3, lanes == ST_BATCH_GROUPED ? 1 : lanes);
+    void* ws = dev(wsb);
+    st_batch* b = nullptr;
+    expect(st_batch_create(chunks.data(), 3, 1.0, 4.0, nullptr, nullptr, lanes, ws, wsb, &b), ST_OK, "st_batch_create");
+    int kernels = 0;
+    expect(st_batch_plan(b, nullptr, nullptr, &kernels), ST_OK, "st_batch_plan");
+    const bool chains = lanes != ST_BATCH_GROUPED;
+    if (g_masked_grads != (chains ? 2 : 0)) hc::violation("%d chunks with cells", g_masked_grads);
+    if (chains && kernels != 3 * 4 + 2 * 2) hc::violation("a plan of %d kernels", kernels);
+    expect(st_batch_launch(b, nullptr), ST_OK, "st_batch_launch");
+    expect(st_batch_destroy(b), ST_OK, "st_batch_destroy");
+    (void)hipFree(ws);
+  }
+  for (st_chunk& c : chunks) {
+    (void)hipFree(const_cast<void*>(c.volume));
+    (void)hipFree(const_cast<uint8_t*>(c.mask));
+    (void)hipFree(c.flags);
+  }
+  // the surrogate
+  if (surrogate_call(129, 251, 263, 40, 0.0) != 4 * 5) hc::violation("layers without cells");
+  setenv("HOSTCHECK_FLAGS", "all", 1);
+  g_outputs.clear();
+  g_any_output = true;  // the fallback's temporaries
+  if (surrogate_call(129, 251, 263, 40, 0.9) != 4 * 5) hc::violation("layers without cells (fallback)");
+  g_any_output = false;
+  unsetenv("HOSTCHECK_FLAGS");
+}
+
+// The re-angling call: 16-byte accesses only where every buffer and plane allows.
+void angles() {
+  for (int64_t nx : {64, 65, 66, 68, 1})
+    for (int shift : {0, 1, 2, 4}) {  // floats past a 16-byte start, bytes past a 4-byte one
+      const int64_t nz = 3, ny = 5, n = nz * ny * nx;
+      float* e3 = static_cast<float*>(dev(4 * (3 * n + 8)));
+      float* ha = static_cast<float*>(dev(4 * (n + 8)));
+      uint8_t* bytes = static_cast<uint8_t*>(dev(2 * n + 16));
+      for (int which = 0; which < 5; ++which) {
+        const int a = which == 0 ? shift : 0, b = which == 1 ? shift : 0, m = which == 2 ? shift : 0,
+                  f = which == 3 ? shift : 0;
+        expect(st_angles(e3 + a, bytes + m, nz, ny, nx, kC, kD, ha + b, nullptr, bytes + n + 8 - (n + 8) % 4 + f, nullptr),
+               ST_OK, "st_angles");
+      }
+      (void)hipFree(e3);
+      (void)hipFree(ha);
+      (void)hipFree(bytes);
+    }
+  if (g_angles != 5 * 4 * 5) hc::violation("%d re-angling launches", g_angles);
+  if (g_wide_angles == 0 || g_wide_angles == g_angles) hc::violation("%d of them wide", g_wide_angles);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -293,6 +374,8 @@ int main(int argc, char** argv) {
   if (what == "threshold") threshold();
   else if (what == "surrogate_threshold") surrogate_threshold();
   else if (what == "split") split();
+  else if (what == "cells") cells();
+  else if (what == "angles") angles();
   else return 2;
   if (hc::live_objects() != 0) {
     std::printf("plans: FAIL (objects leaked)\n");

@@ -64,3 +64,11 @@ def test_surrogate_mask_cells_only_where_they_pay(plans):
 
 def test_gradient_split_targets(plans):
     _run(plans, "split")
+
+
+def test_mask_cells_stay_in_their_buffers(plans):
+    _run(plans, "cells")
+
+
+def test_wide_accesses_of_the_reangling_call(plans):
+    _run(plans, "angles")
