@@ -301,12 +301,11 @@ int check_path_buffers(const PathArgs& a) {
 }
 
 // Voxels from which a mask's cells are made: two small launches, a read of the mask
-// and a gradient pass in runs, which at 162^3 cost 6 % of the call where the mask is
-// full and 2 to 4 % where it is a heart's wall (a ring of half the volume; sigma 0.5
-// to 2, rho 2 to 6).  At 205^3, just above the line, the wall gains up to 2 %, a ball
-// of a third of the volume 4 to 12 % and a full mask loses 3 to 5 %; at 300^3 the
-// wall gains 2 to 8 %, a full mask loses 1 %.
-static constexpr int64_t kMaskCellsMin = int64_t(1) << 23;
+// and a gradient pass in runs.  What they save is the mask's empty part.  At 4 to 8
+// million voxels (26 shapes, sigma 0.8 to 2, rho 2 to 8) a ring in a plane longer than
+// wide takes 0.55 to 0.95 of the time without them, one that fills half of a square
+// plane 1.02 to 1.03, a full mask 1.02 to 1.15.
+static constexpr int64_t kMaskCellsMin = int64_t(1) << 22;
 
 // z pieces of the gradient pass: as many as make the launch shortest, when a piece
 // of c planes costs c + 2R (its halo planes are filtered too) and `tiles` blocks a

@@ -1,4 +1,4 @@
-"""Masked volumes large enough for the mask's cells (2^23 voxels and more), MI355X
+"""Masked volumes of 2^23 voxels and more, well above where the mask's cells begin, MI355X
 only: inside the mask every output equals the unmasked call's bit for bit, outside
 every output is 0 (flags: the outside bit).  The workspace starts as NaNs, so that
 nothing a pass left out can reach an output.  Voxels on both sides of cell and tile

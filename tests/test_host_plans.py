@@ -54,7 +54,7 @@ def _run(exe, group):
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
 
 
-def test_mask_cells_only_where_they_pay(plans):
+def test_mask_cells_from_four_million_voxels(plans):
     _run(plans, "threshold")
 
 
