@@ -90,23 +90,28 @@ __device__ __forceinline__ void head_outputs(const SgConvParams& p, const float 
   if (p.ia) p.ia[vox] = ia;
 }
 
-// z planes per block for `tiles` x-y tiles and `planes` output planes.  A block
-// pays about `head` planes' time before its first output (the ring's first planes,
-// the weights), and per_cu blocks run on a CU, so the launch takes about
-// ceil(blocks / (256 per_cu)) rounds of (chunk + head): the chunk that makes this
-// least, the largest such up to `most`.  A fixed 16 left a 48^3 volume's layers
-// with 18 blocks: 83 us a layer, against 18.  masked: an unknown part of the blocks
-// has work and the rest ends at once, so the chunk is the best for a half, three
-// quarters and all of them together.
+// Rounds of blocks that a launch over `tiles` x-y tiles of `planes` planes takes in z
+// chunks of c, with per_cu blocks on a CU.
+int64_t sg_rounds(int64_t tiles, int64_t planes, int64_t per_cu, int64_t c) {
+  const int64_t cap = 256 * per_cu, blocks = tiles * ((planes + c - 1) / c);
+  return (blocks + cap - 1) / cap;
+}
+
+// z planes per block.  A block pays about kChunkHead planes' time before its first
+// output (the ring's first planes, the weights), so the launch takes about its rounds
+// times (chunk + head): the chunk that makes this least, the largest such up to
+// `most`.  A fixed 16 left a 48^3 volume's layers with 18 blocks: 83 us a layer,
+// against 18.  masked: an unknown part of the blocks has work and the rest ends at
+// once, so the chunk is the best for a half, three quarters and all of them together.
+constexpr int64_t kChunkHead = 3;
 int64_t sg_zchunk(int64_t tiles, int64_t planes, int64_t per_cu, int64_t most, bool masked) {
-  constexpr int64_t kHead = 3;
   const int64_t cap = 256 * per_cu;
   int64_t best = 1, cost = INT64_MAX;
   for (int64_t c = 1; c <= std::min(planes, most); ++c) {
     const int64_t blocks = tiles * ((planes + c - 1) / c);
-    int64_t rounds = (blocks + cap - 1) / cap;
+    int64_t rounds = sg_rounds(tiles, planes, per_cu, c);
     if (masked) rounds += (blocks / 2 + cap - 1) / cap + (3 * blocks / 4 + cap - 1) / cap;
-    const int64_t t = rounds * (c + kHead);
+    const int64_t t = rounds * (c + kChunkHead);
     if (t <= cost) { cost = t; best = c; }
   }
   return best;
@@ -117,6 +122,7 @@ __global__ __launch_bounds__(256) void k_sg_mask_cells(const SgConvParams p) {
   const int64_t cy = sg_cells(p.ny), cx = sg_cells(p.nx);
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i >= sg_cells(p.nz) * cy * cx) return;
+  if (i == 0) *p.work = 0;
   const int64_t x0 = i % cx * kSgCell, y0 = i / cx % cy * kSgCell, z0 = i / (cx * cy) * kSgCell;
   uint32_t any = 0;
 #pragma unroll
@@ -187,6 +193,7 @@ __global__ __launch_bounds__(NT) void k_sg_conv(const SgConvParams p) {
   __shared__ int planes[2];
   masked_planes(p, y0, x0, TY, TX, z0, z1, planes);
   if (z0 >= z1) return;  // block-uniform
+  if (p.work != nullptr && tid == 0) atomicAdd(p.work, static_cast<int>(z1 - z0));
 
   // weights: 16-byte chunks
   {
@@ -362,8 +369,10 @@ __global__ __launch_bounds__(WS_NT) void k_sg_conv_ws(const SgConvParams p) {
   const int64_t yt = b % p.y_tiles;
   const int64_t zc = b / p.y_tiles;
   const int64_t x0 = xt * WS_TX, y0 = yt * WS_TY;
-  int64_t z0 = p.z_lo + zc * p.zchunk;
-  int64_t z1 = (z0 + p.zchunk) < p.z_hi ? (z0 + p.zchunk) : p.z_hi;
+  const int64_t zchunk = p.work != nullptr && *p.work <= p.few ? p.zchunk_few : p.zchunk;
+  int64_t z0 = p.z_lo + zc * zchunk;
+  if (z0 >= p.z_hi) return;  // the grid is that of the shorter chunks
+  int64_t z1 = (z0 + zchunk) < p.z_hi ? (z0 + zchunk) : p.z_hi;
   {
     __shared__ int planes[2];
     const int64_t za = z0, zb = z1;
@@ -587,9 +596,23 @@ hipError_t launch_conv_ws(const SgConvParams& q, hipStream_t stream) {
   SgConvParams p = q;
   p.x_tiles = (p.nx + WS_TX - 1) / WS_TX;
   p.y_tiles = (p.ny + WS_TY - 1) / WS_TY;
-  const int64_t planes = p.z_hi - p.z_lo;
-  p.zchunk = sg_zchunk(p.x_tiles * p.y_tiles, planes, 1, 64, p.cells != nullptr);
-  const int64_t blocks = p.x_tiles * p.y_tiles * ((planes + p.zchunk - 1) / p.zchunk);
+  const int64_t planes = p.z_hi - p.z_lo, tiles = p.x_tiles * p.y_tiles;
+  p.zchunk = sg_zchunk(tiles, planes, 1, 64, false);
+  int64_t chunks = (planes + p.zchunk - 1) / p.zchunk;
+  if (p.work != nullptr) {
+    // Shorter chunks fill the chip where a mask leaves few tiles with work, and cost
+    // another round where it leaves most of them.  Which holds is known on the device
+    // only, so the kernel picks (128^3: a ring 525 us with the short chunks, 490 so, a
+    // full mask 549 and 504; a ring in 316 x 48 x 143 347, 520 with the long ones).
+    p.zchunk_few = sg_zchunk(tiles, planes, 1, 64, true);
+    const auto cost = [&](int64_t t, int64_t c) { return sg_rounds(t, planes, 1, c) * (c + kChunkHead); };
+    int64_t few = tiles;  // the most tiles with work for which they are the better
+    while (few > 0 && cost(few, p.zchunk_few) >= cost(few, p.zchunk)) --few;
+    const int64_t per_tile = p.work_planes * (WS_TY / TY);  // of layer 1's tiles, half as high
+    p.few = few > 0 ? static_cast<int>(std::min<int64_t>(few * per_tile, INT32_MAX)) : -1;
+    if (few > 0) chunks = std::max(chunks, (planes + p.zchunk_few - 1) / p.zchunk_few);
+  }
+  const int64_t blocks = tiles * chunks;
   hipLaunchKernelGGL(k_sg_conv_ws<MODE>, dim3(static_cast<unsigned>(blocks)), dim3(WS_NT), 0, stream, p);
   return hipGetLastError();
 }

@@ -51,6 +51,13 @@ struct SgConvParams {
   uint8_t* cells;
   int build_cells;
   int reach;
+  // With cells: *work is the planes that layer 1 had work in, summed over its tiles,
+  // of the work_planes planes (z) it has been launched over so far; cleared with the
+  // cells.  Layers 2..5 take z chunks of zchunk_few planes where it is at most `few`.
+  int* work;
+  int64_t work_planes;
+  int few;
+  int64_t zchunk_few;
   int has_axis;
   double center[3];
   double dir[3];

@@ -394,16 +394,13 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
   const size_t confb = own_conf ? align256(N * 4) : 0;
   TileGrids grids(nz, ny, nx);
   const size_t flagb = fallback ? align256(grids.total * 4) : 0;
-  // with a mask, the cells that say which tiles the network is needed in.  Below
-  // 2^23 voxels the tiles are too few for the launches to get shorter: with cells a
-  // heart's wall takes 522 us on 128^3 (458 without), 1.56 ms on 192^3 (1.48), a full
-  // mask 548 and 1.64; on 192 x 256 x 256 the wall takes 2.53 ms both ways, a ball 2.18
-  // instead of 2.52, a full mask 2.67 instead of 2.55; on 256 x 320 x 384 the wall
-  // 5.0 instead of 6.7
-  const bool use_cells = mask != nullptr && n >= (int64_t(1) << 23);
+  // with a mask, the cells that say which tiles the network is needed in, and a count
+  // of its work; not below 2^20 voxels, where marking them costs about what it saves
+  const bool use_cells = mask != nullptr && n >= (int64_t(1) << 20);
   const size_t cellb =
       use_cells ? align256(static_cast<size_t>(st::sg_cells(nz) * st::sg_cells(ny) * st::sg_cells(nx))) : 0;
-  const size_t total = w1b + w25b + confb + flagb + cellb;
+  const size_t workb = use_cells ? align256(sizeof(int)) : 0;
+  const size_t total = w1b + w25b + confb + flagb + cellb + workb;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   // the activations (the bulk) serve a whole-volume fallback as its scratch
   char* acts = nullptr;
@@ -427,6 +424,7 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
   float* conf = own_conf ? reinterpret_cast<float*>(take(confb)) : confidence;
   int* dflags = reinterpret_cast<int*>(take(flagb));
   uint8_t* cells = reinterpret_cast<uint8_t*>(take(cellb));
+  int* work = reinterpret_cast<int*>(take(workb));
 
   const float* blob = static_cast<const float*>(weights);
   const char* stage = "surrogate_pack";
@@ -467,6 +465,8 @@ extern "C" int st_surrogate_infer(const void* volume, int dtype, const uint8_t* 
         p.out = layer < st::kSgLayers ? bufs[(layer - 1) & 1] : nullptr;
         p.out_z0 = p.z_lo;
         p.cells = cells;
+        p.work = work;
+        if (layer == 1) p.work_planes += p.z_hi - p.z_lo;
         p.build_cells = za == 0;
         p.reach = static_cast<int>(g);
         p.w = layer >= 2 ? w25 + static_cast<size_t>(layer - 2) * 27 * C * C : nullptr;

@@ -109,11 +109,17 @@ hipError_t wrap_strided(int R, int in_dtype, bool with_d, const StridedParams& p
 hipError_t wrap_conv(int layer, int dtype, const SgConvParams& p, hipStream_t stream) {
   static bool built = false;
   if (layer == 1 && p.z_lo == 0) built = false;
+  if ((p.cells != nullptr) != (p.work != nullptr)) hc::violation("cells without a work count");
   if (p.cells != nullptr) {
     ++g_masked_layers;
     if (p.mask == nullptr) hc::violation("cells without a mask");
     hc::need(p.mask, static_cast<size_t>(p.n), "mask");
     hc::need(p.cells, static_cast<size_t>(sg_cells(p.nz) * sg_cells(p.ny) * sg_cells(p.nx)), "surrogate mask cells");
+    hc::need(p.work, sizeof(int), "surrogate work count");
+    if (reinterpret_cast<uintptr_t>(p.work) % sizeof(int)) hc::violation("an unaligned work count");
+    static int64_t seen = 0;  // planes that layer 1 has been launched over
+    if (layer == 1) seen = p.z_lo == 0 ? p.z_hi : seen + p.z_hi - p.z_lo;
+    if (p.work_planes != seen) hc::violation("work counted over %lld planes, not %lld", (long long)p.work_planes, (long long)seen);
     if (p.reach != kSgLayers - layer) hc::violation("layer %d reaches %d voxels", layer, p.reach);
     if (layer == 1 && p.build_cells) built = true;
     if (!built) hc::violation("layer %d reads cells that no launch made", layer);
@@ -216,11 +222,10 @@ int surrogate_call(int64_t nz, int64_t ny, int64_t nx, int64_t slab, double min_
   return g_masked_layers;
 }
 
-// The surrogate makes its own from 2^23 voxels on, too.
+// The surrogate makes its own from 2^20 voxels on.
 void surrogate_threshold() {
-  if (surrogate_call(128, 128, 128, 32, 0.0) != 0) hc::violation("cells for 128^3");
-  if (surrogate_call(127, 256, 256, 32, 0.0) != 0) hc::violation("cells below 2^23 voxels");
-  if (surrogate_call(128, 256, 256, 32, 0.0) != 4 * 5) hc::violation("no cells at 2^23 voxels in four slabs");
+  if (surrogate_call(127, 64, 128, 32, 0.0) != 0) hc::violation("cells below 2^20 voxels");
+  if (surrogate_call(128, 64, 128, 32, 0.0) != 4 * 5) hc::violation("no cells at 2^20 voxels in four slabs");
 }
 
 // z pieces of the gradient pass for a launch shape.

@@ -58,7 +58,7 @@ def test_mask_cells_from_four_million_voxels(plans):
     _run(plans, "threshold")
 
 
-def test_surrogate_mask_cells_only_where_they_pay(plans):
+def test_surrogate_mask_cells_from_one_million_voxels(plans):
     _run(plans, "surrogate_threshold")
 
 
