@@ -109,7 +109,9 @@ size_t st_workspace_bytes(int64_t nz, int64_t ny, int64_t nx);
  *
  * HA = atan2(f_a sgn f_t, |f_t|) and IA = atan2(f_r sgn f_t, |f_t|) with f_* the
  * components of e3 on the frame e_r (radial), e_t = a x e_r (right-handed) and a
- * (axis), sgn(0) = +1.  Buffers must not overlap each other or the workspace.
+ * (axis), sgn(0) = +1.  Buffers must not overlap each other or the workspace.  What
+ * the outputs hold is undefined until the call's work has finished: a masked call may
+ * keep intermediate results in the first of them.
  */
 int st_compute(const void* volume, int dtype, const uint8_t* mask,
                int64_t nz, int64_t ny, int64_t nx,

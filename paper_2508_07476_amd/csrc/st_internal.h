@@ -130,7 +130,7 @@ constexpr int kXNarrowMaxRadius = 16;    // radii with 16-lane segments of the f
 constexpr bool xfinal_lanes_supported(int R, int lanes) {
   return lanes == 64 || (lanes == 16 && R <= kXNarrowMaxRadius);
 }
-constexpr int kRowsPerBlock = 4;         // rows per block of the angle kernel (one per wave)
+constexpr int kRowsPerBlock = 4;         // rows per block that the host check of the angle launch counts in
 
 hipError_t launch_xgrad(int R, const XGradParams& p, hipStream_t stream);
 hipError_t launch_xfinal(int R, const XFinalParams& p, hipStream_t stream);
@@ -242,7 +242,8 @@ struct AnglesParams {
   float* ha;
   float* ia;
   uint8_t* flags;
-  int64_t n, ny, nx, nrows, x_tiles;
+  int64_t n, ny, nx;
+  int64_t nrows, x_tiles;  // read by the host check only: the kernel takes flat voxels
   int vec_ok;              // n a multiple of 4, e3 and the angles 16-byte, mask and flags 4-byte aligned
   double inv_nx, inv_ny;   // reciprocals, set by launch_angles
   double center[3];
